@@ -6,11 +6,13 @@
 // then ceil((ctx_b - prefix) / S) partitions of the rest.  With M = max lse_p:
 //     w_p = exp(lse_p - M),   out = sum_p w_p o_p / sum_p w_p,
 // which is exactly softmax attention over the whole context (zeros when
-// every w_p is 0).  One wavefront per (b, h).  Lane q loads lse_q (64
-// partitions per round) together with the o rows of the first kGroup
-// partitions, so up to kGroup partitions cost one memory round trip; lane l
-// owns output dims (D/64)*l .. and adds the partitions in order p = 0, 1, ..
-// (weights broadcast from the lane that computed them), so the result is
+// every w_p is 0).  NW wavefronts per (b, h).  Lane q loads lse_q (64
+// partitions per round); the partitions' o rows are dealt to the wavefronts
+// in groups of kGroup, and each wavefront's first group is loaded together
+// with the context length, so up to NW * kGroup partitions cost one memory
+// round trip.  Lane l owns output dims (D/64)*l .. and adds its wavefront's
+// partitions in order (weights broadcast from the lane that computed them),
+// then the wavefronts' sums are added in order through LDS, so the result is
 // deterministic and P_b = 1 reproduces o_0 bit for bit.
 #include "kernels.h"
 #include "pa_device.h"
@@ -18,26 +20,22 @@
 namespace pa {
 namespace {
 
-constexpr int kGroup = 8;   // partitions whose o rows are loaded together
+constexpr int kGroup = 8;   // partitions whose o rows a wavefront loads together
 
-template <int D>
-__global__ void __launch_bounds__(64) reduce_kernel(const ReduceParams p) {
+template <int D, int NW>
+__global__ void __launch_bounds__(64 * NW) reduce_kernel(const ReduceParams p) {
   constexpr int DPL = D / 64;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int wave = wave_uniform(threadIdx.x >> 6);
   const int bh = blockIdx.x;
   const int b = bh / p.num_q_heads;
-  int n = p.context_lens[b] - p.prefix_len;
-  n = n < 0 ? 0 : n;
-  int pb = p.prefix_parts + n / p.part_tokens + (n % p.part_tokens != 0);
-  pb = pb > p.part_stride ? p.part_stride : pb;
   const float* lse = p.part_lse + (size_t)bh * p.part_stride;
   const float* po = p.part_o + (size_t)bh * p.part_stride * D + DPL * lane;
 
-  // o rows of partitions first .. first+kGroup-1 (clamped into the row's
-  // slots; entries past pb are never used)
+  // o rows of partitions first .. first+kGroup-1 (clamped to `lastq`; what
+  // lies past P_b may hold anything and is never used)
   float v[kGroup][DPL];
-  auto load_group = [&](int first) {
-    const int lastq = pb > 0 ? pb - 1 : 0;
+  auto load_group = [&](int first, int lastq) {
 #pragma unroll
     for (int k = 0; k < kGroup; ++k) {
       const int q = min(first + k, lastq);
@@ -45,8 +43,14 @@ __global__ void __launch_bounds__(64) reduce_kernel(const ReduceParams p) {
       for (int d = 0; d < DPL; ++d) v[k][d] = po[(size_t)q * D + d];
     }
   };
-  const float l0 = lane < pb ? lse[lane] : -__builtin_inff();
-  load_group(0);
+  const float x0 = lane < p.part_stride ? lse[lane] : 0.f;
+  load_group(wave * kGroup, p.part_stride - 1);
+
+  int n = p.context_lens[b] - p.prefix_len;
+  n = n < 0 ? 0 : n;
+  int pb = p.prefix_parts + n / p.part_tokens + (n % p.part_tokens != 0);
+  pb = pb > p.part_stride ? p.part_stride : pb;
+  const float l0 = lane < pb ? x0 : -__builtin_inff();
 
   float mx = l0;
   for (int c0 = 64; c0 < pb; c0 += 64)
@@ -61,8 +65,8 @@ __global__ void __launch_bounds__(64) reduce_kernel(const ReduceParams p) {
     const float x = c0 == 0 ? l0 : (c0 + lane < pb ? lse[c0 + lane] : 0.f);
     const int wl = __float_as_int(fast_exp2((x - mref) * kLog2e));   // w of partition c0 + lane
     const int cnt = min(64, pb - c0);
-    for (int j0 = 0; j0 < cnt; j0 += kGroup) {
-      if (c0 + j0 > 0) load_group(c0 + j0);
+    for (int j0 = wave * kGroup; j0 < cnt; j0 += NW * kGroup) {
+      if (c0 + j0 > wave * kGroup) load_group(c0 + j0, pb - 1);
 #pragma unroll
       for (int k = 0; k < kGroup; ++k) {
         if (j0 + k < cnt) {
@@ -74,6 +78,20 @@ __global__ void __launch_bounds__(64) reduce_kernel(const ReduceParams p) {
       }
     }
   }
+  if constexpr (NW > 1) {
+    __shared__ float so[NW][D], sw[NW];
+#pragma unroll
+    for (int d = 0; d < DPL; ++d) so[wave][DPL * lane + d] = o[d];
+    if (lane == 0) sw[wave] = wsum;
+    __syncthreads();
+    if (wave != 0) return;
+#pragma unroll
+    for (int w = 1; w < NW; ++w) {
+      wsum += sw[w];
+#pragma unroll
+      for (int d = 0; d < DPL; ++d) o[d] += so[w][DPL * lane + d];
+    }
+  }
   const float inv = wsum > 0.f ? 1.0f / wsum : 0.f;
   uint16_t* orow = p.out + (size_t)bh * D;
   if constexpr (DPL == 2)
@@ -82,14 +100,27 @@ __global__ void __launch_bounds__(64) reduce_kernel(const ReduceParams p) {
     orow[lane] = (uint16_t)bf16_rne(o[0] * inv);
 }
 
+template <int D>
+void launch_t(const ReduceParams& p, hipStream_t stream) {
+  const dim3 grd((unsigned)((int64_t)p.batch * p.num_q_heads));
+  // One wavefront per row while its single group holds every partition; eight
+  // beyond (1 / 2 / 4 / 8 wavefronts: one sequence of 59 partitions, 64 heads,
+  // whole step 28.2 / 26.6 / 25.9 / 25.4 us; 8192 rows of 16..64 partitions,
+  // whole step 1501 / 1502 / 1501 / 1482 us).
+  constexpr int kWide = 8;
+  if (p.part_stride <= kGroup)
+    hipLaunchKernelGGL((reduce_kernel<D, 1>), grd, dim3(64), 0, stream, p);
+  else
+    hipLaunchKernelGGL((reduce_kernel<D, kWide>), grd, dim3(64 * kWide), 0, stream, p);
+}
+
 }  // namespace
 
 hipError_t launch_reduce(const ReduceParams& p, int head_dim, hipStream_t stream) {
-  const int64_t grid = (int64_t)p.batch * p.num_q_heads;
   if (head_dim == 128)
-    hipLaunchKernelGGL(reduce_kernel<128>, dim3((unsigned)grid), dim3(64), 0, stream, p);
+    launch_t<128>(p, stream);
   else if (head_dim == 64)
-    hipLaunchKernelGGL(reduce_kernel<64>, dim3((unsigned)grid), dim3(64), 0, stream, p);
+    launch_t<64>(p, stream);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
