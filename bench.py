@@ -48,9 +48,9 @@ HBM_PEAK_GBPS = 8000.0
 PROFILE_DIR = os.path.join(ROOT, "profiles")
 _CSRC = "paper_2510_14126_amd/csrc/"
 KERNEL_SOURCES = {
-    "decode_valu": [_CSRC + f for f in ("decode_valu.hip", "valu_body.h", "pa_device.h", "kernels.h")],
-    "decode_mfma": [_CSRC + f for f in ("decode_mfma.hip", "mfma_body.h", "pa_device.h", "kernels.h")],
-    "cascade": [_CSRC + f for f in ("cascade.hip", "valu_body.h", "mfma_body.h", "pa_device.h",
+    "decode_mfma": [_CSRC + f for f in ("decode_mfma.hip", "decode_body.h", "mfma_body.h", "pa_device.h",
+                                        "kernels.h")],
+    "cascade": [_CSRC + f for f in ("cascade.hip", "decode_body.h", "mfma_body.h", "pa_device.h",
                                     "kernels.h")],
     "reduce": [_CSRC + f for f in ("reduce.hip", "pa_device.h", "kernels.h")],
     "append": [_CSRC + f for f in ("append.hip", "pa_device.h", "kernels.h")],
@@ -102,21 +102,19 @@ def launch_configuration(k, w, partition_size=None, prefix_partition_size=None, 
 
 def decode_kernel_of(w, prefix_len: int = 0) -> str:
     """Which decode kernel the library launches for this geometry."""
-    if prefix_len:
-        return "cascade"
-    return "decode_mfma" if (w.group == 8 and w.head_dim == 128) else "decode_valu"
+    return "cascade" if prefix_len else "decode_mfma"
 
 
 def kernel_display_name(w, kernel: str) -> str:
-    return {"cascade": f"cascade_kernel<{w.group}>", "decode_mfma": "decode_mfma_g8_kernel",
-            "decode_valu": f"decode_valu_kernel<{w.head_dim},{w.group}>"}[kernel]
+    return {"cascade": f"cascade_kernel<{w.group}>",
+            "decode_mfma": f"decode_mfma_kernel<{w.head_dim},{w.group}>"}[kernel]
 
 
 def log(msg):
     print(msg, file=sys.stderr, flush=True)
 
 
-def kernel_source_hash(kernel: str = "decode_valu") -> str:
+def kernel_source_hash(kernel: str = "decode_mfma") -> str:
     h = hashlib.sha256()
     for p in KERNEL_SOURCES[kernel]:
         with open(os.path.join(ROOT, p), "rb") as f:
@@ -240,7 +238,7 @@ def cpu_baseline(w, alg_bytes, min_seconds=10.0, logical_bytes=None):
 
 # ------------------------------------------------------------------ traffic
 
-def traffic_from_profiles(workload_name, kernel="decode_valu"):
+def traffic_from_profiles(workload_name, kernel="decode_mfma"):
     """Counter-derived HBM bytes per decode launch, if the profile summary was
     taken on the current kernel source; else None."""
     path = os.path.join(PROFILE_DIR, f"{kernel}_{workload_name}_counters.md")

@@ -168,7 +168,7 @@ int paged_attn_workspace_size(int32_t batch, int32_t num_q_heads, int32_t head_d
  *   partial_out/_lse device fp32 partials (paged_attn_workspace_size), required
  *                    when there is more than one partition; the caller then
  *                    runs paged_attn_reduce on the same stream
- * G = 4 runs on VALU dot products, G = 8 on MFMA tiles.
+ * Both group sizes run on MFMA tiles.
  * Cache policy: when the pool holds no shared block (kv_pool_num_shared is 0),
  * no tile is read twice in a step and the kernels load the tiles with the
  * non-temporal hint; otherwise with the default policy, so that blocks shared

@@ -147,6 +147,7 @@ pa::DecodeParams decode_params(const DecodeArgs& a) {
   p.num_blocks = a.pool->num_blocks;
   p.num_kv_heads = a.pool->num_kv_heads;
   p.num_q_heads = a.num_q_heads;
+  p.head_dim = a.pool->head_dim;
   p.batch = a.batch;
   p.bt_stride = a.bt_stride;
   p.max_ctx = a.max_context_len;
@@ -161,16 +162,6 @@ pa::DecodeParams decode_params(const DecodeArgs& a) {
     p.v_pool_w = a.pool->v;
   }
   return p;
-}
-
-hipError_t launch_decode(const pa::DecodeParams& p, const pa_kv_pool* pool, int32_t group,
-                         bool tracing, void* stream) {
-  // GQA groups of 8 at head_dim 128 form dense 16x16 tiles: matrix cores;
-  // everything else runs on VALU dot products.
-  return (group == 8 && pool->head_dim == 128)
-             ? pa::launch_decode_mfma(p, tracing, static_cast<hipStream_t>(stream))
-             : pa::launch_decode_valu(p, pool->head_dim, group, tracing,
-                                      static_cast<hipStream_t>(stream));
 }
 
 // Checks of an optional host-built work list (items = part * batch + b).
@@ -234,7 +225,7 @@ int decode_impl(const DecodeArgs& a, int32_t partition_size, void* out, float* p
     p.items = items;
     p.num_items = num_items;
   }
-  hipError_t e = launch_decode(p, a.pool, group, tracing, stream);
+  hipError_t e = pa::launch_decode_mfma(p, tracing, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail(PA_EHIP, "%s: kernel launch failed: %s", fn, hipGetErrorString(e));
   return PA_OK;
 }
@@ -643,7 +634,7 @@ int cascade_impl(const pa_kv_pool* pool, const void* q, const int32_t* block_tab
     return PA_OK;
   }
   if (cp.suf_parts > 0) {  // no shared pass (head_dim 64 requires prefix_len 0, no groups)
-    hipError_t e = launch_decode(p, pool, group, tracing, stream);
+    hipError_t e = pa::launch_decode_mfma(p, tracing, st);
     if (e != hipSuccess) return fail(PA_EHIP, "%s: kernel launch failed: %s", fn, hipGetErrorString(e));
   }
   return PA_OK;

@@ -9,28 +9,29 @@
 // instead of preceding it, and workgroup i still serves KV head
 // i % num_kv_heads, which keeps each head on one XCD (the dispatcher deals
 // workgroups to the XCDs round-robin).
+#include "decode_body.h"
 #include "mfma_body.h"
-#include "valu_body.h"
 
 namespace pa {
 namespace {
 
 constexpr int kMax(int a, int b) { return a > b ? a : b; }
-constexpr int kCascadeLds = kMax(kMax(mfma::kPrefixLdsBytes, mfma::kLdsBytes),
-                                 valu::valu_lds_bytes<128, 4, PA_VALU_WAVES>());
+template <int G>
+constexpr int cascade_lds() { return kMax(mfma::kPrefixLdsBytes, decode::lds_bytes<128, G>()); }
 
-static_assert(PA_VALU_WAVES == mfma::kWaves, "both halves use the same workgroup size");
-
-// Tiles in flight per wavefront of the per-sequence half: its work items are
-// the short tails after the prefix, where a 2-deep ring measured ~2% faster
-// than the 3-deep ring of the standalone kernel.
-constexpr int kCascadeValuNbuf = 2;
+// Tiles in flight per wavefront of the per-sequence half: two for the short
+// tails of the G = 4 stages, three for the 512-token items of G = 8.  (Four
+// and four: 64-call generator step 25.0 -> 25.6 us, fixer iteration 50.0 ->
+// 51.3 us, long-context step 1503 -> 1509 us; three and two: 25.6, 50.6 and
+// 1501 us.)
+template <int G>
+constexpr int cascade_nbuf() { return G == 4 ? 2 : 3; }
 
 template <int G, bool TRACE, bool APPEND>
 __global__ void __launch_bounds__(64 * mfma::kWaves) __attribute__((amdgpu_waves_per_eu(2, 8)))
 cascade_kernel(const PrefixParams pp, const DecodeParams dp, int prefix_runs, int group_runs,
                int decode_runs) {
-  __shared__ __attribute__((aligned(16))) uint8_t smem[kCascadeLds];
+  __shared__ __attribute__((aligned(16))) uint8_t smem[cascade_lds<G>()];
   lds_u8_t* lds = (lds_u8_t*)smem;
   // Run r = blockIdx / Hkv: while both kinds remain, even runs are shared
   // runs (the prefix partitions, then the groups) and odd runs decode runs;
@@ -71,12 +72,7 @@ cascade_kernel(const PrefixParams pp, const DecodeParams dp, int prefix_runs, in
     return;
   }
   const int wg = idx * hkv + g;
-  if constexpr (G == 4) {
-    valu::decode_valu_body<128, 4, PA_VALU_WAVES, kCascadeValuNbuf, TRACE, /*STREAM=*/true, APPEND>(
-        dp, wg, lds);
-  } else {
-    mfma::decode_mfma_body<TRACE, /*STREAM=*/true, APPEND>(dp, wg, lds);
-  }
+  decode::decode_body<128, G, cascade_nbuf<G>(), TRACE, /*STREAM=*/true, APPEND>(dp, wg, lds);
 }
 
 }  // namespace

@@ -1,40 +1,62 @@
-// MFMA decode kernels (GQA groups of 8): kernel entry points.  The
-// algorithms live in mfma_body.h; the shared-prefix pass runs inside the
-// cascade kernel (cascade.hip).
-#include "mfma_body.h"
+// Split-KV paged decode attention on MFMA tiles: kernel entry points.  The
+// algorithm lives in decode_body.h; the shared-prefix cascade runs it inside
+// its own kernel (cascade.hip).
+#include "decode_body.h"
 
 namespace pa {
 namespace {
 
 using mfma::kWaves;
 
-template <bool TRACE, bool STREAM, bool APPEND>
-__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 8)))
-decode_mfma_g8_kernel(const DecodeParams p) {
-  __shared__ __attribute__((aligned(16))) uint8_t smem[mfma::kLdsBytes];
-  mfma::decode_mfma_body<TRACE, STREAM, APPEND>(p, blockIdx.x, (lds_u8_t*)smem);
+// Tiles kept in flight per wavefront.  With every tile read once from memory
+// (STREAM) at D = 128, three tiles and two wavefronts per SIMD: 256 sequences
+// of 64..8192 tokens take 238 us, against 251 us with two tiles and three
+// wavefronts.  Where sequences share blocks the tiles come from L2, the items
+// are short of latency hiding, not of bandwidth, and two tiles (154 VGPRs:
+// three wavefronts per SIMD) win: 64 sequences over a shared 2048-token
+// prefix 47.7 -> 42.6 us.  At D = 64 a tile is half the bytes: four tiles at
+// three wavefronts (130 VGPRs) against five at two: 4 sequences of 100..300
+// tokens 5.3 -> 5.0 us, 48 of 61..4093 tokens 30.6 -> 30.0 us.
+template <int D, bool STREAM>
+constexpr int nbuf() { return D == 64 ? 4 : (STREAM ? 3 : 2); }
+
+template <int D, int G, bool TRACE, bool STREAM, bool APPEND>
+__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2, 8)))
+decode_mfma_kernel(const DecodeParams p) {
+  __shared__ __attribute__((aligned(16))) uint8_t smem[decode::lds_bytes<D, G>()];
+  decode::decode_body<D, G, nbuf<D, STREAM>(), TRACE, STREAM, APPEND>(p, blockIdx.x, (lds_u8_t*)smem);
+}
+
+// The trace kernel keeps the default cache policy (the hint changes no
+// index) and has no fused append.
+template <int D, int G>
+hipError_t launch_t(const DecodeParams& p, bool trace, hipStream_t stream) {
+  const int64_t grid = decode_items(p) * p.num_kv_heads;
+  if (grid == 0) return hipSuccess;
+  const dim3 grd((unsigned)grid), blk(64 * kWaves);
+  const bool append = p.k_new != nullptr;
+  if (trace)
+    hipLaunchKernelGGL((decode_mfma_kernel<D, G, true, false, false>), grd, blk, 0, stream, p);
+  else if (p.stream_tiles && append)
+    hipLaunchKernelGGL((decode_mfma_kernel<D, G, false, true, true>), grd, blk, 0, stream, p);
+  else if (p.stream_tiles)
+    hipLaunchKernelGGL((decode_mfma_kernel<D, G, false, true, false>), grd, blk, 0, stream, p);
+  else if (append)
+    hipLaunchKernelGGL((decode_mfma_kernel<D, G, false, false, true>), grd, blk, 0, stream, p);
+  else
+    hipLaunchKernelGGL((decode_mfma_kernel<D, G, false, false, false>), grd, blk, 0, stream, p);
+  return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_decode_mfma(const DecodeParams& p, bool trace, hipStream_t stream) {
-  const int64_t grid = decode_items(p) * p.num_kv_heads;
-  if (grid == 0) return hipSuccess;
-  // The trace kernel keeps the default cache policy (the hint changes no
-  // index) and has no fused append.
-  const dim3 grd((unsigned)grid), blk(64 * kWaves);
-  const bool append = p.k_new != nullptr;
-  if (trace)
-    hipLaunchKernelGGL((decode_mfma_g8_kernel<true, false, false>), grd, blk, 0, stream, p);
-  else if (p.stream_tiles && append)
-    hipLaunchKernelGGL((decode_mfma_g8_kernel<false, true, true>), grd, blk, 0, stream, p);
-  else if (p.stream_tiles)
-    hipLaunchKernelGGL((decode_mfma_g8_kernel<false, true, false>), grd, blk, 0, stream, p);
-  else if (append)
-    hipLaunchKernelGGL((decode_mfma_g8_kernel<false, false, true>), grd, blk, 0, stream, p);
-  else
-    hipLaunchKernelGGL((decode_mfma_g8_kernel<false, false, false>), grd, blk, 0, stream, p);
-  return hipGetLastError();
+  const int group = p.num_q_heads / p.num_kv_heads;
+  if (p.head_dim == 128 && group == 4) return launch_t<128, 4>(p, trace, stream);
+  if (p.head_dim == 128 && group == 8) return launch_t<128, 8>(p, trace, stream);
+  if (p.head_dim == 64 && group == 4) return launch_t<64, 4>(p, trace, stream);
+  if (p.head_dim == 64 && group == 8) return launch_t<64, 8>(p, trace, stream);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace pa

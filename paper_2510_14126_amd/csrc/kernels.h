@@ -22,7 +22,8 @@ struct DecodeParams {
   int32_t* trace;                // index trace (trace variant only)
   int32_t num_blocks;
   int32_t num_kv_heads;
-  int32_t num_q_heads;
+  int32_t num_q_heads;           // 4 or 8 per KV head
+  int32_t head_dim;              // 64 or 128
   int32_t batch;
   int32_t bt_stride;
   int32_t max_ctx;
@@ -135,13 +136,9 @@ struct ReduceParams {
   int32_t prefix_len;            // tokens covered by those partitions
 };
 
-// VALU split-KV decode (group size 4 or 8, head_dim 64 or 128).
-hipError_t launch_decode_valu(const DecodeParams& p, int head_dim, int group, bool trace,
-                              hipStream_t stream);
-// MFMA split-KV decode for group size 8, head_dim 128.
+// Split-KV decode (group size 4 or 8, head_dim 64 or 128).
 hipError_t launch_decode_mfma(const DecodeParams& p, bool trace, hipStream_t stream);
-// Shared-prefix pass and per-sequence decode in one launch (head_dim 128;
-// the decode half uses VALU for group 4 and MFMA for group 8).
+// Shared-prefix pass and per-sequence decode in one launch (head_dim 128).
 hipError_t launch_cascade(const PrefixParams& pp, const DecodeParams& dp, int group, bool trace,
                           hipStream_t stream);
 // Log-sum-exp merge of split-KV partials into the bf16 output.

@@ -42,46 +42,23 @@ namespace pa {
 namespace mfma {
 
 
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef short short4_t __attribute__((ext_vector_type(4)));
+typedef float floatx2_t __attribute__((ext_vector_type(2)));
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) short4_t lds_short4_t;
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) u32x4_t lds_u32x4_t;
 
 constexpr int kD = 128;
-constexpr int kG = 8;
 constexpr int kWaves = 4;
 constexpr int kKPitch = kD * 2;               // LDS bytes per staged K token row (swizzled, k_stage)
-constexpr int kStageBytes = 16 * kKPitch;     // one staged K tile
 constexpr float kLazyRescale = 8.0f;
-#ifndef PA_MFMA_NBUF
-#define PA_MFMA_NBUF 3
-#endif
-constexpr int kNbuf = PA_MFMA_NBUF;  // tiles kept in flight per wavefront
-
-struct MfmaTile {
-  uint4 k[4];  // [u]: row 4u+q, 16-byte chunk n of the K tile
-  uint4 v[4];  // [u]: row 4u+q, chunk n of the V tile
-};
-
-
-// Rows 4u+q, chunk n of one K or V tile (lane_off = the byte offset of row q,
-// chunk n) through a buffer descriptor built from the wave-uniform tile
-// address; `bytes` = 0 makes the loads no-ops that return zeros but still
-// count as issued.  AUX: the loads' cache policy (kLoadDefault or
-// kLoadStreaming).
-template <int AUX>
-__device__ __forceinline__ void load_chunks(uint4 (&dst)[4], const uint16_t* tile, uint32_t lane_off,
-                                            int bytes) {
-  const __amdgpu_buffer_rsrc_t rsrc =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(tile), 0, bytes, kBufferDescWord3);
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const auto x =
-        __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)lane_off + u * 4 * kD * 2, 0, AUX);
-    dst[u] = make_uint4(x[0], x[1], x[2], x[3]);
-  }
+// Two fp32 values rounded to nearest even as a packed bf16 pair.
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  const floatx2_t x = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2_t));
 }
 
 // Value of query column 4q+r (held by lane 4q+r) for the accumulator rows
@@ -100,116 +77,8 @@ template <int NT>
 struct MfmaState {
   float m[NT];        // running max of query column n (log2 units), same in all groups
   float l[NT];        // this lane's share of the column sum (tokens 4q..4q+3 of each block)
-  floatx4_t o[NT][8]; // [j]: O[rows 4q+r][dim 8n + j] (tile_core) or [dim 16j + n] (tile_core_nb)
+  floatx4_t o[NT][8]; // [j]: O[rows 4q+r][dim 16j + n]
 };
-
-// One 16-token block against NT column tiles that share the K and V
-// operands (their MFMA chains are independent and interleave).
-// ka[s]: A operand of k-step s (token 4(n%4) + n/4, chunk 4s+q of the K
-// tile); vrow[u]: the lane's V registers (token 4u+q, chunk n); `valid`:
-// tokens of this tile that exist (V rows past it are zeroed); `limit[t]`:
-// tokens this lane's column of tile t may attend to (<= valid).
-template <bool TAIL, int NT>
-__device__ __forceinline__ void tile_core(MfmaState<NT>& S, const u32x4_t (&ka)[4],
-                                          const uint4 (&vrow)[4], const uint4 (&qb)[NT][4],
-                                          int valid, const int (&limit)[NT], int q,
-                                          float scale_log2) {
-
-  // Two independent accumulation chains per tile, summed at the end.
-  floatx4_t st[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const floatx4_t z = {0.f, 0.f, 0.f, 0.f};
-    floatx4_t a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-        __builtin_bit_cast(bf16x8_t, ka[0]), __builtin_bit_cast(bf16x8_t, qb[t][0]), z, 0, 0, 0);
-    floatx4_t b = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-        __builtin_bit_cast(bf16x8_t, ka[1]), __builtin_bit_cast(bf16x8_t, qb[t][1]), z, 0, 0, 0);
-    a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ka[2]),
-                                                __builtin_bit_cast(bf16x8_t, qb[t][2]), a, 0, 0, 0);
-    b = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ka[3]),
-                                                __builtin_bit_cast(bf16x8_t, qb[t][3]), b, 0, 0, 0);
-    st[t] = a + b;
-  }
-
-  // Scores of tokens 4r+q; the rescale test needs no cross-lane reduction:
-  // any lane above its column's max + kLazyRescale triggers it.
-  float sc[NT][4];
-  bool raise = false;
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      float x = st[t][r] * scale_log2;
-      if (TAIL && 4 * r + q >= limit[t]) x = -__builtin_inff();
-      sc[t][r] = x;
-      raise |= x > S.m[t] + kLazyRescale;
-    }
-  }
-  if (__builtin_amdgcn_ballot_w64(raise) != 0) {
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const float bm = group_max4(fmaxf(fmaxf(sc[t][0], sc[t][1]), fmaxf(sc[t][2], sc[t][3])));
-      const float mn = bm > S.m[t] + kLazyRescale ? bm : S.m[t];
-      // 1 for columns that keep their max (or have attended to nothing yet)
-      const float alpha = mn == -__builtin_inff() ? 1.f : fast_exp2(S.m[t] - mn);
-      S.l[t] *= alpha;
-      S.m[t] = mn;
-      // Accumulator rows are indexed by lane group: row 4q+r takes alpha of
-      // column 4q+r, held by lane 4q+r.
-      float ar[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) ar[r] = column_value(alpha, q, r);
-#pragma unroll
-      for (int blk = 0; blk < 8; ++blk)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) S.o[t][blk][r] *= ar[r];
-    }
-  }
-
-  // Probabilities as bf16 pairs for the matrix core: p = hi + lo, hi = bf16(p)
-  // and lo = bf16(p - hi) (the difference is exact in fp32), so the PV
-  // product sees each weight to about 2^-17 relative; the column sum adds the
-  // fp32 values.
-  short4_t pa[NT], pl[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const float mref = S.m[t] == -__builtin_inff() ? 0.f : S.m[t];  // fully masked: p = 0
-    float ps = 0.f;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const float pf = fast_exp2(sc[t][r] - mref);
-      const __bf16 hi = (__bf16)pf;
-      pa[t][r] = __builtin_bit_cast(short, hi);
-      pl[t][r] = __builtin_bit_cast(short, (__bf16)(pf - (float)hi));
-      ps += pf;
-    }
-    S.l[t] += ps;
-  }
-
-  // PV: instruction j takes B = V[token 4e+q][dim 8n+j], e = 0..3: bf16 j of
-  // the lane's chunk in each of its four rows.  Tail rows become zero.
-  uint32_t vw[4][4];
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const bool keep = !(TAIL && 4 * u + q >= valid);
-    vw[u][0] = keep ? vrow[u].x : 0u;
-    vw[u][1] = keep ? vrow[u].y : 0u;
-    vw[u][2] = keep ? vrow[u].z : 0u;
-    vw[u][3] = keep ? vrow[u].w : 0u;
-  }
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u;
-    const uint32_t lo = __builtin_amdgcn_perm(vw[1][j >> 1], vw[0][j >> 1], sel);
-    const uint32_t hi = __builtin_amdgcn_perm(vw[3][j >> 1], vw[2][j >> 1], sel);
-    const short4_t vb = __builtin_bit_cast(short4_t, make_uint2(lo, hi));
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      S.o[t][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa[t], vb, S.o[t][j], 0, 0, 0);
-      S.o[t][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pl[t], vb, S.o[t][j], 0, 0, 0);
-    }
-  }
-}
 
 // Row of the K tile that lane (q, n) supplies as A row n: token 4(n%4) + n/4.
 __device__ __forceinline__ int k_arow(int n) { return 4 * (n & 3) + (n >> 2); }
@@ -429,220 +298,6 @@ __device__ __forceinline__ void tile_core_nb(MfmaState<NT>& S, const lds_u8_t* s
   }
 }
 
-
-// One block of a per-sequence work item: the wavefront's own K tile goes
-// through `stage` (kStageBytes of its LDS) to reach the A-operand layout;
-// V is used from the registers it was loaded into.
-template <bool TAIL, int NT>
-__device__ __forceinline__ void process_tile(MfmaState<NT>& S, const MfmaTile& T,
-                                             const uint4 (&qb)[NT][4], lds_u8_t* stage, int valid,
-                                             const int (&limit)[NT], int q, int n,
-                                             float scale_log2) {
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const u32x4_t k = {T.k[u].x, T.k[u].y, T.k[u].z, T.k[u].w};
-    *reinterpret_cast<lds_u32x4_t*>(stage + k_stage(4 * u + q, n)) = k;
-  }
-  u32x4_t ka[4];
-#pragma unroll
-  for (int s = 0; s < 4; ++s)
-    ka[s] = *reinterpret_cast<const lds_u32x4_t*>(stage + k_stage(k_arow(n), 4 * s + q));
-  tile_core<TAIL, NT>(S, ka, T.v, qb, valid, limit, q, scale_log2);
-}
-
-// LDS bytes either body needs (two staged K tiles per wavefront, then the
-// end-of-item merge).
-constexpr int kMergeLdsBytes = (2 * kWaves * 16 + kWaves * 16 * kD) * 4;  // up to 16 rows per wave
-constexpr int kLdsBytes = kWaves * 2 * kStageBytes > kMergeLdsBytes ? kWaves * 2 * kStageBytes
-                                                                    : kMergeLdsBytes;
-
-// One decode work item (partition, sequence, KV head) = workgroup `wg_index`.
-// STREAM: load the tiles as streaming data (the cascade's per-sequence half,
-// whose tokens come after everything the sequences share and are normally
-// read by this item only).  The hint changes caching, never the results.
-// APPEND: the fused KV append (DecodeParams::k_new): the item that holds
-// token ctx - 1 takes its K and V rows from k_new / v_new in registers
-// (whatever the pool slot holds) and stores them into the slot.
-template <bool TRACE, bool STREAM, bool APPEND = false>
-__device__ __forceinline__ void decode_mfma_body(const DecodeParams& p, int wg_index, lds_u8_t* smem) {
-  const int lane = threadIdx.x & 63;
-  const int wave = wave_uniform(threadIdx.x >> 6);
-  const int q = lane >> 4;
-  const int n = lane & 15;
-
-  int g, b, part;
-  decode_item(p, wg_index, g, b, part);
-
-  const int start = p.token_offset + part * p.part_tokens;
-  const int j0 = start >> 4;
-  const int h0 = g * kG;
-  const int32_t* bt = p.block_tables + (size_t)b * p.bt_stride + j0;
-  // The first 64 block ids and the query rows are loaded before the context
-  // length arrives (j0 < bt_stride for every launched partition).
-  const int raw_first = lane < min(64, p.bt_stride - j0) ? bt[lane] : 0;
-
-  // Q^T operand: column n holds query row n % 8; dims 32s + 8q .. +8.
-  uint4 qb[1][4];
-  {
-    const uint16_t* qrow = p.q + ((size_t)b * p.num_q_heads + h0 + (n & 7)) * kD;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) qb[0][s] = *reinterpret_cast<const uint4*>(qrow + (4 * s + q) * 8);
-  }
-
-  int ctx = p.context_lens[b];
-  ctx = ctx < 0 ? 0 : (ctx > p.max_ctx ? p.max_ctx : ctx);
-  const bool split = p.write_partials != 0;
-  if (split && start >= ctx) return;
-  const int end = min(ctx, start + p.part_tokens);
-  const int nblk = end > start ? (end - start + 15) >> 4 : 0;
-
-  // Fused append: block jnew of this item (-1: none) holds the new token in
-  // row rnew; knew / vnew are chunk n (dims 8n .. 8n+7) of its K and V rows.
-  // The lanes of row group rnew % 4 store the rows.
-  int jnew = -1, rnew = 0;
-  uint4 knew = make_uint4(0, 0, 0, 0), vnew = make_uint4(0, 0, 0, 0);
-  if constexpr (APPEND) {
-    if (ctx > 0 && ctx - 1 >= start && ctx - 1 < end) {
-      jnew = ((ctx - 1) >> 4) - j0;
-      rnew = (ctx - 1) & 15;
-      const size_t src = ((size_t)b * p.num_kv_heads + g) * kD + 8 * n;
-      knew = *reinterpret_cast<const uint4*>(p.k_new + src);
-      vnew = *reinterpret_cast<const uint4*>(p.v_new + src);
-      if (wave == 0 && q == (rnew & 3)) {
-        int phys = p.block_tables[(size_t)b * p.bt_stride + ((ctx - 1) >> 4)];
-        phys = min(max(phys, 0), p.num_blocks - 1);
-        const size_t dst = (((size_t)phys * p.num_kv_heads + g) * 16 + rnew) * kD + 8 * n;
-        *reinterpret_cast<uint4*>(p.k_pool_w + dst) = knew;
-        *reinterpret_cast<uint4*>(p.v_pool_w + dst) = vnew;
-      }
-    }
-  }
-
-  lds_u8_t* lds = smem;
-  lds_u8_t* stages[2] = {lds + (wave * 2) * kStageBytes, lds + (wave * 2 + 1) * kStageBytes};
-
-  MfmaState<1> S;
-  S.m[0] = -__builtin_inff();
-  S.l[0] = 0.f;
-#pragma unroll
-  for (int blk = 0; blk < 8; ++blk) S.o[0][blk] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-
-  constexpr size_t kTileElems = 16 * kD;
-  const size_t blk_stride = (size_t)p.num_kv_heads * kTileElems;
-  const uint16_t* kbase = p.k_pool + (size_t)g * kTileElems;
-  const uint16_t* vbase = p.v_pool + (size_t)g * kTileElems;
-  const size_t item = ((size_t)part * p.batch + b) * p.num_kv_heads + g;
-  const uint32_t lane_off = (uint32_t)(q * kD + n * 8) * 2u;  // row q, chunk n (+ 4 rows per u)
-  int flip = 0;
-
-  for (int c0 = 0; c0 < nblk; c0 += 64) {
-    const int cn = min(64, nblk - c0);
-    const int raw = c0 == 0 ? (lane < cn ? raw_first : 0) : (lane < cn ? bt[c0 + lane] : 0);
-    const int idc = min(max(raw, 0), p.num_blocks - 1);
-    auto load = [&](MfmaTile& T, int i) {
-      const bool ok = i < cn;
-      const size_t id = (size_t)__builtin_amdgcn_readlane(idc, ok ? i : 0);
-      const int bytes = ok ? (int)(kTileElems * 2) : 0;
-      constexpr int kAux = STREAM ? kLoadStreaming : kLoadDefault;
-      load_chunks<kAux>(T.k, kbase + id * blk_stride, lane_off, bytes);
-      load_chunks<kAux>(T.v, vbase + id * blk_stride, lane_off, bytes);
-    };
-    auto run = [&](MfmaTile& T, int i) {
-      const int valid = min(16, end - (start + (c0 + i) * 16));
-      if constexpr (APPEND) {
-        // the new token's rows replace whatever the slot held (the ring slot
-        // is loaded again before its next use)
-        if (c0 + i == jnew) {
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (4 * u + q == rnew) { T.k[u] = knew; T.v[u] = vnew; }
-        }
-      }
-      lds_u8_t* vb = stages[flip];
-      flip ^= 1;
-      const int lim[1] = {valid};
-      if (valid == 16)
-        process_tile<false, 1>(S, T, qb, vb, 16, lim, q, n, p.scale_log2);
-      else
-        process_tile<true, 1>(S, T, qb, vb, valid, lim, q, n, p.scale_log2);
-      if constexpr (TRACE) {
-        if (lane == 0) {
-          int32_t* tr = p.trace + (item * p.trace_tiles + (c0 + i)) * 3;
-          tr[0] = j0 + c0 + i;
-          tr[1] = __builtin_amdgcn_readlane(raw, i);
-          tr[2] = valid;
-        }
-      }
-    };
-
-    int i = wave;
-    if (i >= cn) continue;
-    MfmaTile T[kNbuf];
-    int ld = i;
-#pragma unroll
-    for (int s = 0; s < kNbuf - 1; ++s) {
-      load(T[s], ld);
-      ld += kWaves;
-    }
-    bool done = false;
-    while (!done) {
-#pragma unroll
-      for (int s = 0; s < kNbuf; ++s) {
-        if (!done) {
-          load(T[(s + kNbuf - 1) % kNbuf], ld);
-          ld += kWaves;
-          run(T[s], i);
-          i += kWaves;
-          done = i >= cn;
-        }
-      }
-    }
-  }
-
-  // Merge the waves through LDS (the staging area is free now).
-  const float lrow = group_sum4(S.l[0]);
-  __syncthreads();
-  lds_f32_t* sm = reinterpret_cast<lds_f32_t*>(smem);       // [W][8]
-  lds_f32_t* sl = sm + kWaves * kG;                          // [W][8]
-  lds_f32_t* sacc = sl + kWaves * kG;                        // [W][8][128]
-  if (q == 0 && n < kG) { sm[wave * kG + n] = S.m[0]; sl[wave * kG + n] = lrow; }
-  if (q < 2) {
-#pragma unroll
-    for (int blk = 0; blk < 8; ++blk)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        sacc[(wave * kG + 4 * q + r) * kD + 8 * n + blk] = S.o[0][blk][r];
-  }
-  __syncthreads();
-  if (wave != 0) return;
-
-#pragma unroll
-  for (int r = 0; r < kG; ++r) {
-    float mx = sm[r];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) mx = fmaxf(mx, sm[w * kG + r]);
-    const float mref = (mx == -__builtin_inff()) ? 0.f : mx;
-    float lt = 0.f, o0 = 0.f, o1 = 0.f;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      const float f = fast_exp2(sm[w * kG + r] - mref);
-      lt = fmaf(sl[w * kG + r], f, lt);
-      const float2 a = {sacc[(w * kG + r) * kD + 2 * lane], sacc[(w * kG + r) * kD + 2 * lane + 1]};
-      o0 = fmaf(a.x, f, o0);
-      o1 = fmaf(a.y, f, o1);
-    }
-    const float inv = lt > 0.f ? 1.0f / lt : 0.f;
-    if (!split) {
-      uint16_t* orow = p.out + ((size_t)b * p.num_q_heads + h0 + r) * kD;
-      *reinterpret_cast<uint32_t*>(orow + 2 * lane) = bf16_rne(o0 * inv) | (bf16_rne(o1 * inv) << 16);
-    } else {
-      const size_t row = ((size_t)b * p.num_q_heads + h0 + r) * p.part_stride + p.part_offset + part;
-      store_partial2(p.part_o + row * kD + 2 * lane, o0 * inv, o1 * inv);
-      if (lane == 0)
-        p.part_lse[row] = lt > 0.f ? (mx + log2f(lt)) * kLn2 : -__builtin_inff();
-    }
-  }
-}
 
 // Attention over the prefix that every sequence of the batch shares: for KV
 // head g the B*G query rows form the columns of dense 16-row tiles (four

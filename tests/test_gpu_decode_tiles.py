@@ -1,0 +1,71 @@
+"""The matrix-core decode at the edges of its tiles, for every geometry it
+takes (head_dim 64 and 128, four and eight query heads per KV head) and for
+negative and zero scales: contexts of 0 and 1 tokens, around one block, around
+one round of the four wavefronts, around the 64 block ids read at a time, and
+an item's masked last block on each wavefront.  Poison past every context;
+outputs against the oracle under the parity gate."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from oracle import compare, decode_workload  # noqa: E402
+from workloads import f32_to_bf16_bits, logical_case, page_case  # noqa: E402
+
+CTX = [0, 1, 15, 16, 17, 33, 48, 63, 64, 65, 81, 127, 1009, 1023, 1024, 1025, 1041, 2064, 2100]
+
+
+@pytest.mark.parametrize("scale", [None, -0.2, 0.0])
+@pytest.mark.parametrize("S", [0, 64, 1040])
+@pytest.mark.parametrize("d,hq,hkv", [(64, 8, 2), (64, 24, 3), (128, 12, 3), (128, 8, 1)])
+def test_tile_edges(d, hq, hkv, S, scale):
+    from paper_2510_14126_amd.device import PagedBatch
+    print(f"[gpu case] tile edges D={d} Hq={hq} Hkv={hkv} S={S} scale={scale}", flush=True)
+    w = page_case(logical_case(400 + d + hq, len(CTX), hq, hkv, d, CTX, scale=scale), 401, poison=True)
+    ref = decode_workload(w)[0]
+    outs = []
+    for shared in (False, True):           # both cache policies (and ring depths)
+        pb = PagedBatch(w, "cuda:0", partition_size=S)
+        if shared:
+            from paper_2510_14126_amd import binding
+            binding.kv_pool_retain(pb.pool, [int(w.block_tables[-1, 0])])
+        pb.out.fill_(0x7FC0)               # NaN bits: every row must be written
+        pb.run()
+        torch.cuda.synchronize()
+        outs.append(pb.out_bits())
+        pb.close()
+    rep = compare(outs[0], ref)
+    assert rep.passed, f"{rep}"
+    assert np.array_equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("d,hq,hkv", [(64, 8, 2), (64, 24, 3), (128, 12, 3), (128, 8, 1)])
+def test_fused_append_in_every_row(d, hq, hkv):
+    """The appended token in each row of a block, as the last row of a whole
+    block and as the first of a new one, and past 64 blocks."""
+    from oracle import append_kv
+    from paper_2510_14126_amd.device import PagedBatch
+    ctx = list(range(1, 18)) + [64, 65, 1024, 1025, 1040]
+    print(f"[gpu case] fused append D={d} Hq={hq} Hkv={hkv}", flush=True)
+    w = page_case(logical_case(420 + d + hq, len(ctx), hq, hkv, d, ctx), 421, poison=True)
+    rng = np.random.default_rng(422)
+    new = [f32_to_bf16_bits(rng.standard_normal((len(ctx), hkv, d), dtype=np.float32)) for _ in range(2)]
+    for b, n in enumerate(ctx):            # what the slot holds beforehand is never used
+        w.k_pool[w.block_tables[b, (n - 1) // 16], :, (n - 1) % 16] = 0x7FC0
+        w.v_pool[w.block_tables[b, (n - 1) // 16], :, (n - 1) % 16] = 0x7FC0
+    for S in (0, 512):
+        pb = PagedBatch(w, "cuda:0", partition_size=S)
+        pb.decode_append(*(torch.from_numpy(x.view(np.int16)).cuda() for x in new))
+        if pb.needs_reduce:
+            pb.reduce()
+        torch.cuda.synchronize()
+        out, k, v = pb.out_bits(), pb.k.cpu().numpy().view(np.uint16), pb.v.cpu().numpy().view(np.uint16)
+        pb.close()
+        wk, wv = append_kv(w.k_pool, w.v_pool, w.block_tables, w.context_lens, new[0], new[1])
+        assert np.array_equal(k, wk) and np.array_equal(v, wv)
+        rep = compare(out, decode_workload(replace(w, k_pool=wk, v_pool=wv))[0])
+        assert rep.passed, f"S={S}: {rep}"
