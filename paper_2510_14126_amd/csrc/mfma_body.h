@@ -1,38 +1,19 @@
-// Split-KV paged decode attention on MFMA tiles for GQA groups of 8 (gfx950).
+// Matrix-core pieces shared by the kernels (gfx950), and attention over token
+// spans that many query rows share (head_dim 128).
 //
-// With eight query heads per KV head, QK^T and PV of a 16-token block are
-// dense enough for the matrix cores:
-//
-//  * Both tiles of a block are read from the pool in row order: each 16-lane
-//    group takes one whole 256-byte token row, so a load instruction reads
-//    1 KiB of contiguous memory and the vector L1 sees one access per 64
-//    bytes.  (Reading the MFMA operand layout straight from the pool would
-//    put 16 different rows in every 16-lane group, about one L1 access per
-//    lane, and the L1 becomes the limit when the tiles come from L2.)  Lane
-//    (q, n) = (lane >> 4, lane & 15) then holds tokens 4u+q (u = 0..3),
-//    dims 8n .. 8n+7, of both tiles.
-//  * S^T = K Q^T with v_mfma_f32_16x16x32_bf16: A = K rows (16 tokens x 32
-//    dims per instruction, 4 instructions for D = 128) read back from an LDS
-//    copy of the K tile (k_stage: XOR-swizzled 256-byte rows, so writes and
-//    reads spread over the banks); B = Q^T with the query rows in its 16
-//    columns.  A row i
-//    is token 4(i%4) + i/4, so lane (q, n) receives the scores of tokens
-//    4r+q (r = 0..3) for query column n.
-//  * O += P V with v_mfma_f32_16x16x16bf16_1k, one per 8 output dims: the
-//    contraction index k = 4q+e stands for token 4e+q, which makes the
-//    scores above exactly the A operand (P never moves between lanes), and
-//    output column n of instruction j is dim 8n + j, which makes the B
-//    operand V[token 4e+q][dim 8n+j] element j of the lane's own V registers
-//    (two v_perm_b32 per instruction; V never goes through LDS).
+// Query rows form the 16 columns of dense tiles; the blocks of the span are
+// staged in LDS in whole 256-byte token rows (reading the MFMA operand layout
+// straight from the pool would put 16 different rows in every 16-lane group,
+// about one L1 access per lane) and every wavefront runs its tile against
+// them (tile_core_nb).
 //
 // The online softmax keeps one running max per query row, replicated over the
-// four lane groups, and rescales the accumulator only when a block raises the
+// four lane groups, and rescales the accumulator only when a stage raises the
 // max by more than kLazyRescale (log2 units): probabilities stay <= 2^8, the
 // rescale branch is wave-uniform and rare.  Each probability reaches the
 // matrix core as a bf16 pair (high part and the rounded remainder, two MFMAs
 // per PV step), which carries it to about 2^-17 relative; the row sum adds the
 // fp32 values.
-// Tail rows are removed by select: score -inf and V row zero.
 #pragma once
 
 #include "kernels.h"
@@ -40,7 +21,6 @@
 
 namespace pa {
 namespace mfma {
-
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
@@ -55,11 +35,14 @@ constexpr int kD = 128;
 constexpr int kWaves = 4;
 constexpr int kKPitch = kD * 2;               // LDS bytes per staged K token row (swizzled, k_stage)
 constexpr float kLazyRescale = 8.0f;
+
 // Two fp32 values rounded to nearest even as a packed bf16 pair.
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   const floatx2_t x = {a, b};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2_t));
 }
+
+template <bool B> struct BoolTag { static constexpr bool value = B; };
 
 // Value of query column 4q+r (held by lane 4q+r) for the accumulator rows
 // of lane group q.
@@ -76,6 +59,7 @@ __device__ __forceinline__ float column_value(float x, int q, int r) {
 template <int NT>
 struct MfmaState {
   float m[NT];        // running max of query column n (log2 units), same in all groups
+  float neg[NT];      // -m, or 0 while m is -inf
   float l[NT];        // this lane's share of the column sum (tokens 4q..4q+3 of each block)
   floatx4_t o[NT][8]; // [j]: O[rows 4q+r][dim 16j + n]
 };
@@ -153,12 +137,11 @@ static_assert(1 <= kExtendLoadAhead && kExtendLoadAhead <= kExtendRingSets, "loa
 // the lane's v_tr offset).  valid[b]: rows of block b that hold tokens of the
 // span (0: an empty block); lim[t][b]: rows of block b that column n of
 // tile t may see.  Rows past valid[b] are zeroed in the B operand (their V may be
-// anything, NaN included).  With FOLD (scale_log2 >= 0 required) the scale
-// is applied inside the exponent's FMA, and the running-max test uses the
-// lane's largest unmasked raw score times the scale (the same value as the
-// largest scaled score, since multiplying by a non-negative number keeps
-// the order).
-template <bool TAIL, int NB, int NT, bool FOLD = false>
+// anything, NaN included).  scale_log2 >= 0: the scale is applied inside the
+// exponent's FMA, and the running-max test uses the lane's largest unmasked
+// raw score times the scale (the same value as the largest scaled score,
+// since multiplying by a non-negative number keeps the order).
+template <bool TAIL, int NB, int NT>
 __device__ __forceinline__ void tile_core_nb(MfmaState<NT>& S, const lds_u8_t* st, int vtr,
                                              const uint4 (&qb)[NT][4], const int (&valid)[NB],
                                              const int (&lim)[NT][NB], int q, int n, float scale_log2) {
@@ -173,6 +156,7 @@ __device__ __forceinline__ void tile_core_nb(MfmaState<NT>& S, const lds_u8_t* s
 #pragma unroll
     for (int c = 0; c < 4; ++c)
       ka[b][c] = *reinterpret_cast<const lds_u32x4_t*>(st + b * kPrefixStageBytes + k_stage(k_arow(n), 4 * c + q));
+  __builtin_amdgcn_s_setprio(1);
   floatx4_t a[NT][NB];
 #pragma unroll
   for (int t = 0; t < NT; ++t)
@@ -188,47 +172,33 @@ __device__ __forceinline__ void tile_core_nb(MfmaState<NT>& S, const lds_u8_t* s
       for (int b = 0; b < NB; ++b)
         a[t][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ka[b][c]),
                                                           __builtin_bit_cast(bf16x8_t, qb[t][c]), a[t][b], 0, 0, 0);
+  __builtin_amdgcn_s_setprio(0);
 
-  // Probabilities of tile t as bf16 pairs (the A operands: element e of
-  // pa[t][p] and pl[t][p] is the high and low part of the weight of score
-  // 8p + e, p = hi + lo to about 2^-17 relative); the column sum adds the fp32
-  // values.
-  bf16x8_t pa[NT][NB / 2], pl[NT][NB / 2];
+  // One rescale branch for all tiles: it is rare, and what follows it is
+  // straight-line code that the scheduler can interleave across tiles.
+  float xmax[NT];   // NaN when all are masked and the scale is 0
+  bool raise = false;
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    float sc[4 * NB];   // scaled scores, or raw ones with FOLD
-    bool raise = false;
-    float mx = -__builtin_inff();   // FOLD: the lane's largest unmasked raw score
+    float mx = -__builtin_inff();   // the lane's largest unmasked raw score
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        if constexpr (FOLD) {
-          const float raw = a[t][b][r];
-          sc[4 * b + r] = raw;
-          if (!TAIL || 4 * r + q < lim[t][b]) mx = fmaxf(mx, raw);
-        } else {
-          float x = a[t][b][r] * scale_log2;
-          if (TAIL && 4 * r + q >= lim[t][b]) x = -__builtin_inff();
-          sc[4 * b + r] = x;
-          raise |= x > S.m[t] + kLazyRescale;
-        }
-      }
-    const float xmax = mx * scale_log2;   // FOLD only (NaN when all are masked and the scale is 0)
-    if constexpr (FOLD) raise = xmax > S.m[t] + kLazyRescale;
-    if (__builtin_amdgcn_ballot_w64(raise) != 0) {
-      float bmax = sc[0];
-      if constexpr (FOLD) {
-        bmax = xmax;
-      } else {
+      for (int r = 0; r < 4; ++r)
+        if (!TAIL || 4 * r + q < lim[t][b]) mx = fmaxf(mx, a[t][b][r]);
+    xmax[t] = mx * scale_log2;
+    raise |= xmax[t] > S.m[t] + kLazyRescale;
+  }
+  if (__builtin_amdgcn_ballot_w64(raise) != 0) {
 #pragma unroll
-        for (int e = 1; e < 4 * NB; ++e) bmax = fmaxf(bmax, sc[e]);
-      }
-      const float bm = group_max4(bmax);
+    for (int t = 0; t < NT; ++t) {
+      const float bm = group_max4(xmax[t]);
       const float mn = bm > S.m[t] + kLazyRescale ? bm : S.m[t];
+      // 1 for columns that keep their max (or have attended to nothing yet)
       const float alpha = mn == -__builtin_inff() ? 1.f : fast_exp2(S.m[t] - mn);
       S.l[t] *= alpha;
       S.m[t] = mn;
+      S.neg[t] = mn == -__builtin_inff() ? 0.f : -mn;
       float ar[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) ar[r] = column_value(alpha, q, r);
@@ -237,29 +207,36 @@ __device__ __forceinline__ void tile_core_nb(MfmaState<NT>& S, const lds_u8_t* s
 #pragma unroll
         for (int r = 0; r < 4; ++r) S.o[t][blk][r] *= ar[r];
     }
+  }
 
-    const float mref = S.m[t] == -__builtin_inff() ? 0.f : S.m[t];
-    float lsum = 0.f;
+  // Probabilities of tile t as bf16 pairs (the A operands: element e of
+  // pa[t][p] and pl[t][p] is the high and low part of the weight of score
+  // 8p + e, p = hi + lo to about 2^-17 relative); the column sum adds the fp32
+  // values.
+  u32x4_t pa[NT][NB / 2], pl[NT][NB / 2];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    float sum = 0.f;
 #pragma unroll
     for (int pp = 0; pp < NB / 2; ++pp) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        float ex;
-        if constexpr (FOLD) {
-          ex = fmaf(sc[8 * pp + e], scale_log2, -mref);
-          // element e is token 4(e % 4) + q of block 2pp + e / 4
-          if (TAIL && 4 * (e & 3) + q >= lim[t][2 * pp + (e >> 2)]) ex = -__builtin_inff();
-        } else {
-          ex = sc[8 * pp + e] - mref;
+      for (int e = 0; e < 8; e += 2) {
+        float pf[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          // element e + i is token 4((e+i) % 4) + q of block 2pp + (e+i) / 4
+          const int b = 2 * pp + ((e + i) >> 2), r = (e + i) & 3;
+          float ex = fmaf(a[t][b][r], scale_log2, S.neg[t]);
+          if (TAIL && 4 * r + q >= lim[t][b]) ex = -__builtin_inff();
+          pf[i] = fast_exp2(ex);
         }
-        const float pf = fast_exp2(ex);
-        const __bf16 hi = (__bf16)pf;
-        pa[t][pp][e] = hi;
-        pl[t][pp][e] = (__bf16)(pf - (float)hi);
-        lsum += pf;
+        const uint32_t hi = pack_bf16(pf[0], pf[1]);
+        pa[t][pp][e / 2] = hi;
+        pl[t][pp][e / 2] = pack_bf16(pf[0] - bf16_lo(hi), pf[1] - bf16_hi(hi));
+        sum += pf[0] + pf[1];
       }
     }
-    S.l[t] += lsum;
+    S.l[t] += sum;
   }
 
   // Element e of a block's B words is its token 4e + q.
@@ -273,29 +250,50 @@ __device__ __forceinline__ void tile_core_nb(MfmaState<NT>& S, const lds_u8_t* s
       mhi[b] = (q + 8 < valid[b] ? 0xffffu : 0u) | (q + 12 < valid[b] ? 0xffff0000u : 0u);
     }
   }
-  // Each B operand (two transposing reads) serves the NT tiles.
+  // Each B operand (two transposing reads) serves the NT tiles.  The operands
+  // of kPvGroup output columns are read together and their high-part MFMAs
+  // issued before the low-part ones, so that no MFMA waits for its own LDS
+  // read or for the MFMA just before it; the MFMAs run at raised priority, so
+  // that a wavefront in its softmax does not hold them up.  (64-call
+  // generator step, one wavefront per SIMD in this pass: groups of 1 / 2 / 4
+  // columns 24.9 / 24.4 / 24.3 us, and with the priority 24.6 / 24.5 / 23.9;
+  // before, 25.1.)
+  constexpr int kPvGroup = 4;
+  __builtin_amdgcn_s_setprio(1);
 #pragma unroll
   for (int pp = 0; pp < NB / 2; ++pp) {
     const lds_u8_t* v0 = st + (2 * pp) * kPrefixStageBytes + kPrefixKBytes;
     const lds_u8_t* v1 = v0 + kPrefixStageBytes;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int off = vtr ^ (j << 5);
-      const uint2 b0 = __builtin_bit_cast(
-          uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_t*)(v0 + off)));
-      const uint2 b1 = __builtin_bit_cast(
-          uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_t*)(v1 + off)));
-      const u32x4_t vb = {b0.x & mlo[2 * pp], b0.y & mhi[2 * pp], b1.x & mlo[2 * pp + 1],
-                          b1.y & mhi[2 * pp + 1]};
+    for (int j = 0; j < 8; j += kPvGroup) {
+      u32x4_t vb[kPvGroup];
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        S.o[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa[t][pp], __builtin_bit_cast(bf16x8_t, vb),
-                                                            S.o[t][j], 0, 0, 0);
-        S.o[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl[t][pp], __builtin_bit_cast(bf16x8_t, vb),
-                                                            S.o[t][j], 0, 0, 0);
+      for (int i = 0; i < kPvGroup; ++i) {
+        const int off = vtr ^ ((j + i) << 5);
+        const uint2 b0 = __builtin_bit_cast(
+            uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_t*)(v0 + off)));
+        const uint2 b1 = __builtin_bit_cast(
+            uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_t*)(v1 + off)));
+        vb[i] = u32x4_t{b0.x & mlo[2 * pp], b0.y & mhi[2 * pp], b1.x & mlo[2 * pp + 1],
+                        b1.y & mhi[2 * pp + 1]};
       }
+#pragma unroll
+      for (int i = 0; i < kPvGroup; ++i)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          S.o[t][j + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pa[t][pp]),
+                                                                  __builtin_bit_cast(bf16x8_t, vb[i]),
+                                                                  S.o[t][j + i], 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < kPvGroup; ++i)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          S.o[t][j + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pl[t][pp]),
+                                                                  __builtin_bit_cast(bf16x8_t, vb[i]),
+                                                                  S.o[t][j + i], 0, 0, 0);
     }
   }
+  __builtin_amdgcn_s_setprio(0);
 }
 
 
@@ -347,6 +345,10 @@ __device__ __forceinline__ void shared_span_body(const PrefixParams& p, int g, c
   const int idc = min(max(raw, 0), p.num_blocks - 1);
 
   // Column n is query row R = row0 + n: sequence seq0 + R / G, head g*G + R % G.
+  // A negative scale goes into the sign of Q (bf16 negation is exact, and so
+  // is the negation of every score): the core needs a non-negative one.
+  const uint32_t qflip = p.scale_log2 < 0.f ? 0x80008000u : 0u;
+  const float scale_abs = fabsf(p.scale_log2);
   uint4 qb[1][4];
   int ctx;
   int min_ctx;
@@ -356,8 +358,11 @@ __device__ __forceinline__ void shared_span_body(const PrefixParams& p, int g, c
     const int bR = ok ? sp.seq0 + R / G : 0;
     const uint16_t* qrow = p.q + ((size_t)bR * p.num_q_heads + g * G + R % G) * kD;
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
-      qb[0][s] = ok ? *reinterpret_cast<const uint4*>(qrow + (4 * s + q) * 8) : make_uint4(0, 0, 0, 0);
+    for (int s = 0; s < 4; ++s) {
+      uint4 w = ok ? *reinterpret_cast<const uint4*>(qrow + (4 * s + q) * 8) : make_uint4(0, 0, 0, 0);
+      w.x ^= qflip; w.y ^= qflip; w.z ^= qflip; w.w ^= qflip;
+      qb[0][s] = w;
+    }
     int c = ok ? p.context_lens[bR] : 0;
     c = c < 0 ? 0 : (c > p.max_ctx ? p.max_ctx : c);
     ctx = c;
@@ -367,6 +372,7 @@ __device__ __forceinline__ void shared_span_body(const PrefixParams& p, int g, c
 
   MfmaState<1> S;
   S.m[0] = -__builtin_inff();
+  S.neg[0] = 0.f;
   S.l[0] = 0.f;
 #pragma unroll
   for (int blk = 0; blk < 8; ++blk) S.o[0][blk] = floatx4_t{0.f, 0.f, 0.f, 0.f};
@@ -447,9 +453,9 @@ __device__ __forceinline__ void shared_span_body(const PrefixParams& p, int g, c
           }
         }
         if (fast)
-          tile_core_nb<false, NB>(S, st, vtr, qb, valid, lim, q, n, p.scale_log2);
+          tile_core_nb<false, NB>(S, st, vtr, qb, valid, lim, q, n, scale_abs);
         else
-          tile_core_nb<true, NB>(S, st, vtr, qb, valid, lim, q, n, p.scale_log2);
+          tile_core_nb<true, NB>(S, st, vtr, qb, valid, lim, q, n, scale_abs);
       }
     }
   }
@@ -548,7 +554,6 @@ __device__ __forceinline__ void group_mfma_body(const PrefixParams& p, int wg_in
 // wavefront's tiles; the stream stops at the workgroup's last visible token.
 // Each wavefront normalises its rows and writes them as bf16.
 constexpr int kExtendTilesPerWave = kExtendRowsPerWg / (16 * kWaves);
-template <bool B> struct BoolTag { static constexpr bool value = B; };
 static_assert(kExtendTilesPerWave * 16 * kWaves == kExtendRowsPerWg, "whole tiles per wavefront");
 constexpr int kExtendIdOffset = 2 * kExtendStageBlocks * kPrefixStageBytes;   // after two stages
 constexpr int kExtendLdsBytes = kExtendIdOffset + kExtendMaxTokens / 16 * 4;   // + the block ids
@@ -625,6 +630,7 @@ __device__ __forceinline__ void extend_mfma_body(const ExtendParams& p, int wg_i
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     S.m[t] = -__builtin_inff();
+    S.neg[t] = 0.f;
     S.l[t] = 0.f;
 #pragma unroll
     for (int blk = 0; blk < 8; ++blk) S.o[t][blk] = floatx4_t{0.f, 0.f, 0.f, 0.f};
@@ -701,7 +707,7 @@ __device__ __forceinline__ void extend_mfma_body(const ExtendParams& p, int wg_i
 #pragma unroll
         for (int t = 0; t < NT; ++t) lim[t][s] = min(valid[s], max(lim_col[t] - tb, 0));
       }
-      tile_core_nb<TAIL, NB, NT, true>(S, st, vtr, qb, valid, lim, q, n, scale_abs);
+      tile_core_nb<TAIL, NB, NT>(S, st, vtr, qb, valid, lim, q, n, scale_abs);
     }
   }
   }
