@@ -1,6 +1,6 @@
 // Extend (chunked prefill) attention over the paged cache: kernel entry
-// point.  The algorithm lives in extend_mfma_body (mfma_body.h).
-#include "mfma_body.h"
+// point.  The algorithm lives in extend_body.h.
+#include "extend_body.h"
 
 namespace pa {
 namespace {
@@ -8,8 +8,8 @@ namespace {
 template <int G>
 __global__ void __launch_bounds__(64 * mfma::kWaves) __attribute__((amdgpu_waves_per_eu(2, 8)))
 extend_mfma_kernel(const ExtendParams p) {
-  __shared__ __attribute__((aligned(16))) uint8_t smem[mfma::kExtendLdsBytes];
-  mfma::extend_mfma_body<G>(p, blockIdx.x, (lds_u8_t*)smem);
+  __shared__ __attribute__((aligned(16))) uint8_t smem[extend::kLdsBytes];
+  extend::extend_body<G>(p, blockIdx.x, (lds_u8_t*)smem);
 }
 
 }  // namespace

@@ -42,8 +42,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2_t));
 }
 
-template <bool B> struct BoolTag { static constexpr bool value = B; };
-
 // Value of query column 4q+r (held by lane 4q+r) for the accumulator rows
 // of lane group q.
 __device__ __forceinline__ float column_value(float x, int q, int r) {
@@ -99,29 +97,16 @@ __device__ __forceinline__ int v_tr(int q, int n) {
   return r * 256 + (v_swz(r) << 5) + ((n & 3) << 3);
 }
 
-// One staged block in the shared-span pass and extend: its K tile (k_stage
-// layout) then its V tile (v_stage layout).
+// One staged block in the shared-span pass: its K tile (k_stage layout) then
+// its V tile (v_stage layout).
 constexpr int kPrefixKBytes = 16 * kKPitch;
 constexpr int kPrefixStageBytes = kPrefixKBytes + 16 * kD * 2;
-// The shared-prefix pass streams its blocks in pairs (one LDS stage and one
-// barrier per pair) through a ring of kPrefixRing quarter-blocks: the first
-// pair is loaded before the loop and each pair's successor while it is
-// published.  Extend streams kExtendStageBlocks blocks per stage through
-// kExtendRingSets sets of slots, each stage loaded kExtendLoadAhead stages
-// before it is published (1 <= AHEAD <= SETS; stage j in set j % SETS).
-// Measured fastest: the prefix pass as described (the generic loop at the
-// same depth was 4% slower on the generator batch), extend at (2, 2, 2)
-// (with one tile per wavefront that form needed 162 VGPRs and ran three
-// wavefronts per SIMD; two tiles per wavefront need 218 and run two, and
-// are faster).
+// The pass streams its blocks in pairs (one LDS stage and one barrier per
+// pair) through a ring of kPrefixRing quarter-blocks: the first pair is loaded
+// before the loop and each pair's successor while it is published.
 constexpr int kPrefixStageBlocks = 2;
 constexpr int kPrefixRing = 4;
-constexpr int kExtendStageBlocks = 2;
-constexpr int kExtendRingSets = 2;
-constexpr int kExtendLoadAhead = 2;
 static_assert(kPrefixRing == 2 * kPrefixStageBlocks, "two pairs of slots");
-static_assert(kExtendStageBlocks % 2 == 0, "blocks go in pairs");
-static_assert(1 <= kExtendLoadAhead && kExtendLoadAhead <= kExtendRingSets, "loads stay in the ring");
 
 // NB 16-token blocks (NB even) staged at st + b * kPrefixStageBytes (K in the
 // k_stage layout, V in the v_stage layout) against NT column tiles, which
@@ -540,197 +525,6 @@ __device__ __forceinline__ void group_mfma_body(const PrefixParams& p, int wg_in
   if constexpr (TRACE)
     tr = p.trace_group + ((size_t)k * p.num_kv_heads + g) * p.group_trace_tiles * 3;
   shared_span_body<G, TRACE>(p, g, sp, smem, tr);
-}
-
-// Causal attention of a chunk of new tokens over its sequence's paged
-// context (extend / chunked prefill).  For KV head g, the (chunk token i,
-// head j) pairs of sequence b form rows R = i*G + j of dense 16-row tiles;
-// row R sees the tokens 0 .. n - L + i (n: context with the chunk, L: chunk
-// length), which is the per-column limit the MFMA core already applies.
-// One workgroup owns kExtendRowsPerWg rows, kExtendTilesPerWave adjacent
-// tiles per wavefront, and streams the sequence's blocks once through LDS
-// for all of them, as the shared-prefix pass does, two blocks per barrier
-// through tile_core_nb, whose K and V operand reads serve all of a
-// wavefront's tiles; the stream stops at the workgroup's last visible token.
-// Each wavefront normalises its rows and writes them as bf16.
-constexpr int kExtendTilesPerWave = kExtendRowsPerWg / (16 * kWaves);
-static_assert(kExtendTilesPerWave * 16 * kWaves == kExtendRowsPerWg, "whole tiles per wavefront");
-constexpr int kExtendIdOffset = 2 * kExtendStageBlocks * kPrefixStageBytes;   // after two stages
-constexpr int kExtendLdsBytes = kExtendIdOffset + kExtendMaxTokens / 16 * 4;   // + the block ids
-
-template <int G>
-__device__ __forceinline__ void extend_mfma_body(const ExtendParams& p, int wg_index, lds_u8_t* smem) {
-  const int lane = threadIdx.x & 63;
-  const int wave = wave_uniform(threadIdx.x >> 6);
-  const int q = lane >> 4;
-  const int n = lane & 15;
-
-  int wg = wg_index;
-  const int g = wg % p.num_kv_heads;
-  wg /= p.num_kv_heads;
-  const int grp = wg % p.groups;
-  const int b = wg / p.groups;
-
-  int ctx = p.context_lens[b];
-  ctx = ctx < 0 ? 0 : (ctx > p.max_ctx ? p.max_ctx : ctx);
-  int qs = p.q_start[b];
-  int L = p.q_start[b + 1] - qs;
-  qs = qs < 0 ? 0 : qs;
-  L = L < 0 ? 0 : (L > ctx ? ctx : (L > p.max_chunk ? p.max_chunk : L));
-  L = qs + L > p.total_q ? (p.total_q > qs ? p.total_q - qs : 0) : L;
-  const int rows = L * G;
-  if (grp * kExtendRowsPerWg >= rows) return;          // whole workgroup: no rows here
-  constexpr int NT = kExtendTilesPerWave;
-  const int row0 = grp * kExtendRowsPerWg + 16 * NT * wave;   // this wavefront's first tile
-  const int first = ctx - L;                           // position of chunk token 0
-
-  // Tokens the workgroup needs: up to its last row's position.
-  const int last_row = min(rows, (grp + 1) * kExtendRowsPerWg) - 1;
-  const int vis_max = first + last_row / G + 1;
-  const int nblk = (vis_max + 15) >> 4;
-
-  // Block ids of the stream, clamped into the pool, staged once in LDS
-  // (at most kExtendMaxTokens / 16 of them); each is read back as a
-  // broadcast when its block is loaded.
-  lds_i32_t* ids = reinterpret_cast<lds_i32_t*>(smem + kExtendIdOffset);
-  {
-    const int32_t* bt = p.block_tables + (size_t)b * p.bt_stride;
-    for (int j = threadIdx.x; j < nblk; j += 64 * kWaves)
-      ids[j] = min(max(bt[j], 0), p.num_blocks - 1);
-    __syncthreads();
-  }
-  auto block_id = [&](int i) { return __builtin_amdgcn_readfirstlane(ids[i]); };
-
-  // Column n of tile t is row R = row0 + 16t + n: chunk token R / G, query
-  // head g*G + R % G.  A negative scale goes into the sign of Q (bf16
-  // negation is exact, and so is the negation of every score), so the core
-  // folds a non-negative scale into its exponent.
-  const uint32_t qflip = p.scale_log2 < 0.f ? 0x80008000u : 0u;
-  const float scale_abs = fabsf(p.scale_log2);
-  uint4 qb[NT][4];
-  int lim_col[NT];   // tokens column n of tile t sees
-  {
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int R = row0 + 16 * t + n;
-      const bool ok = R < rows;
-      const int i = ok ? R / G : 0;
-      const uint16_t* qrow = p.q + ((size_t)(qs + i) * p.num_q_heads + g * G + R % G) * kD;
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        uint4 w = ok ? *reinterpret_cast<const uint4*>(qrow + (4 * s + q) * 8) : make_uint4(0, 0, 0, 0);
-        w.x ^= qflip; w.y ^= qflip; w.z ^= qflip; w.w ^= qflip;
-        qb[t][s] = w;
-      }
-      lim_col[t] = ok ? first + i + 1 : 0;
-    }
-  }
-
-  MfmaState<NT> S;
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    S.m[t] = -__builtin_inff();
-    S.neg[t] = 0.f;
-    S.l[t] = 0.f;
-#pragma unroll
-    for (int blk = 0; blk < 8; ++blk) S.o[t][blk] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-  }
-
-  constexpr size_t kTileElems = 16 * kD;
-  const size_t blk_stride = (size_t)p.num_kv_heads * kTileElems;
-  const int share_off = ((4 * wave + q) * kD + n * 8) * 2;   // token row 4*wave + q, chunk n
-  const int vtr = v_tr(q, n);
-  const uint16_t* kbase = p.k_pool + (size_t)g * kTileElems;
-  const uint16_t* vbase = p.v_pool + (size_t)g * kTileElems;
-  auto load = [&](uint4 (&dst)[2], int i) {
-    const bool ok = i < nblk;
-    const size_t id = (size_t)block_id(ok ? i : 0);
-    const int bytes = ok ? (int)(kTileElems * 2) : 0;
-    const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t*>(kbase + id * blk_stride), 0, bytes, kBufferDescWord3);
-    const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t*>(vbase + id * blk_stride), 0, bytes, kBufferDescWord3);
-    const auto k = __builtin_amdgcn_raw_buffer_load_b128(rk, share_off, 0, 0);
-    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rv, share_off, 0, 0);
-    dst[0] = make_uint4(k[0], k[1], k[2], k[3]);
-    dst[1] = make_uint4(v[0], v[1], v[2], v[3]);
-  };
-
-  // The blocks go NB at a time: every wavefront publishes its quarter of
-  // each block of stage j to one LDS stage (double-buffered), loads the
-  // quarters of stage j + AHEAD, one barrier, then every wavefront runs its
-  // tiles against the stage.  Blocks past the stream are empty (valid = 0).
-  constexpr int NB = kExtendStageBlocks;
-  constexpr int SETS = kExtendRingSets;
-  constexpr int AHEAD = kExtendLoadAhead;
-  uint4 ring[SETS * NB][2];                     // stage j's blocks in slot set j % SETS
-#pragma unroll
-  for (int s = 0; s < AHEAD * NB; ++s) load(ring[s], s);
-  const int nit = (nblk + NB - 1) / NB;
-  // Stages 0 .. nfast-1 are wholly visible to every row of the workgroup
-  // (its first row sees the fewest tokens) and run unmasked in a loop of
-  // their own; the rest, up to the causal diagonal, run masked in a second
-  // loop.  One core per loop keeps the compiler from copying the output
-  // accumulators where the two cores' paths would otherwise merge.  nfast
-  // is a multiple of SETS so that both loops find stage j in slot set
-  // j % SETS.
-  const int wg_min_lim = first + grp * kExtendRowsPerWg / G + 1;
-  int nfast = min(wg_min_lim, vis_max) / (16 * NB);
-  nfast = min(nfast - nfast % SETS, nit);
-  auto stream = [&](auto tail, int jb, int je) {
-  constexpr bool TAIL = decltype(tail)::value;
-  for (int j0 = jb; j0 < je; j0 += SETS) {
-#pragma unroll
-  for (int h = 0; h < SETS; ++h) {
-    const int j = j0 + h;
-    if (j < je) {                               // uniform over the workgroup
-      lds_u8_t* st = smem + (j & 1) * NB * kPrefixStageBytes;
-#pragma unroll
-      for (int s = 0; s < NB; ++s) {
-        lds_u8_t* sb = st + s * kPrefixStageBytes;
-        const uint4 (&rs)[2] = ring[h * NB + s];
-        *reinterpret_cast<lds_u32x4_t*>(sb + k_stage(4 * wave + q, n)) =
-            u32x4_t{rs[0].x, rs[0].y, rs[0].z, rs[0].w};
-        *reinterpret_cast<lds_u32x4_t*>(sb + kPrefixKBytes + v_stage(4 * wave + q, n)) =
-            u32x4_t{rs[1].x, rs[1].y, rs[1].z, rs[1].w};
-      }
-#pragma unroll
-      for (int s = 0; s < NB; ++s) load(ring[((h + AHEAD) % SETS) * NB + s], NB * (j + AHEAD) + s);
-      __syncthreads();
-
-      int valid[NB], lim[NT][NB];
-      const int t0 = NB * j * 16;
-#pragma unroll
-      for (int s = 0; s < NB; ++s) {
-        const int tb = t0 + 16 * s;
-        valid[s] = max(0, min(16, vis_max - tb));
-#pragma unroll
-        for (int t = 0; t < NT; ++t) lim[t][s] = min(valid[s], max(lim_col[t] - tb, 0));
-      }
-      tile_core_nb<TAIL, NB, NT>(S, st, vtr, qb, valid, lim, q, n, scale_abs);
-    }
-  }
-  }
-  };
-  stream(BoolTag<false>{}, 0, nfast);
-  stream(BoolTag<true>{}, nfast, nit);
-
-  // Normalise and write bf16: lane (q, n) holds O[rows 4q+r of tile t][dims 16j + n].
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const float lcol = group_sum4(S.l[t]);
-    const float inv = lcol > 0.f ? 1.0f / lcol : 0.f;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int R = row0 + 16 * t + 4 * q + r;
-      const float f = column_value(inv, q, r);
-      if (R < rows) {
-        uint16_t* orow = p.out + ((size_t)(qs + R / G) * p.num_q_heads + g * G + R % G) * kD + n;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) orow[16 * j] = (uint16_t)bf16_rne(S.o[t][j][r] * f);
-      }
-    }
-  }
 }
 
 }  // namespace mfma
