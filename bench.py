@@ -50,8 +50,8 @@ _CSRC = "paper_2510_14126_amd/csrc/"
 KERNEL_SOURCES = {
     "decode_mfma": [_CSRC + f for f in ("decode_mfma.hip", "decode_body.h", "mfma_body.h", "pa_device.h",
                                         "kernels.h")],
-    "cascade": [_CSRC + f for f in ("cascade.hip", "decode_body.h", "mfma_body.h", "pa_device.h",
-                                    "kernels.h")],
+    "cascade": [_CSRC + f for f in ("cascade.hip", "decode_body.h", "shared_body.h", "shared_rows_body.h",
+                                    "mfma_body.h", "pa_device.h", "kernels.h")],
     "reduce": [_CSRC + f for f in ("reduce.hip", "pa_device.h", "kernels.h")],
     "append": [_CSRC + f for f in ("append.hip", "pa_device.h", "kernels.h")],
     "extend": [_CSRC + f for f in ("extend.hip", "extend_body.h", "mfma_body.h", "pa_device.h", "kernels.h")],

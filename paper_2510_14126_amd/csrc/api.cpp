@@ -557,10 +557,11 @@ int cascade_impl(const pa_kv_pool* pool, const void* q, const int32_t* block_tab
   }
   const int64_t rows = (int64_t)batch * num_q_heads;
   // Upper bound on the fused grid: a prefix workgroup covers at least 16 query
-  // rows of one KV head, a suffix workgroup one (sequence, KV head) pair.
+  // rows of one KV head, a group (at most 64 rows) takes at most two, a suffix
+  // workgroup is one (sequence, KV head) pair.
   const int64_t g_pre = (int64_t)cp.pre_parts * ((rows / pool->num_kv_heads + 15) / 16) * pool->num_kv_heads;
   const int64_t g_suf = (int64_t)cp.suf_parts * batch * pool->num_kv_heads;
-  const int64_t g_grp = group_len > 0 ? (int64_t)num_groups * pool->num_kv_heads : 0;
+  const int64_t g_grp = group_len > 0 ? (int64_t)num_groups * 2 * pool->num_kv_heads : 0;
   if (g_pre + g_grp + g_suf > 0x7fffffffLL)
     return fail(PA_EINVAL, "%s: grid too large", fn);
   if (scheduled) {

@@ -68,6 +68,8 @@ using mfma::floatx4_t;
 using mfma::k_arow;
 using mfma::kLazyRescale;
 using mfma::kWaves;
+using mfma::lds_floatx2_t;
+using mfma::lds_floatx4_t;
 using mfma::lds_u32x4_t;
 using mfma::pack_bf16;
 using mfma::short4_t;
@@ -75,8 +77,6 @@ using mfma::u32x4_t;
 
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) u32x2_t lds_u32x2_t;
-typedef __attribute__((address_space(3))) floatx2_t lds_floatx2_t;
-typedef __attribute__((address_space(3))) floatx4_t lds_floatx4_t;
 
 // Tile ring of a wavefront: D / 32 dwords per lane and token row.
 template <int D>

@@ -53,15 +53,15 @@ namespace pa {
 namespace extend {
 
 using mfma::bf16x8_t;
+using mfma::floatx16_t;
 using mfma::kLazyRescale;
 using mfma::kWaves;
+using mfma::lds_floatx4_t;
 using mfma::lds_short4_t;
 using mfma::lds_u32x4_t;
 using mfma::pack_bf16;
 using mfma::u32x4_t;
 
-typedef float floatx16_t __attribute__((ext_vector_type(16)));
-typedef __attribute__((address_space(3))) mfma::floatx4_t lds_floatx4_t;
 typedef int i32x2_t __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) i32x2_t lds_i32x2_t;
 

@@ -106,7 +106,7 @@ struct PrefixParams {
   // tokens after the prefix; its partial is partition prefix_parts.
   const int32_t* group_start;    // device [num_groups + 1]
   int32_t num_groups;
-  int32_t max_group_size;        // max_group_size * G <= 64 (one workgroup per group)
+  int32_t max_group_size;        // max_group_size * G <= 64
   int32_t group_len;             // a multiple of 16, at most 1024
   float scale_log2;
   // Index trace (trace launches only): the tiles of prefix partition part,
@@ -120,7 +120,8 @@ struct PrefixParams {
 };
 
 // Query rows (sequence x head of one KV head) per workgroup of the shared
-// passes: four wavefronts, one 16-row tile each.
+// passes, and per row group of their index trace.
+constexpr int kSharedTileRows = 32;
 constexpr int kSharedRowsPerWg = 64;
 
 struct ReduceParams {

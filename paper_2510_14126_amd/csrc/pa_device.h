@@ -45,6 +45,16 @@ __device__ __forceinline__ void store_partial2(float* dst, float a, float b) {
   __hip_atomic_store(reinterpret_cast<uint64_t*>(dst), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Four floats at dst (16-byte aligned) in one store of the same scope, for
+// which there is no atomic type.  The wait state keeps the next instruction
+// from overwriting the data registers too early (gfx9: one after a vector
+// store of more than 64 bits).
+typedef float store_f4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void store_partial4(float* dst, float a, float b, float c, float d) {
+  const store_f4_t v = {a, b, c, d};
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(dst), "v"(v) : "memory");
+}
+
 // Cache-policy operand of a buffer load: bit 1 is the non-temporal hint of
 // the gfx940 family.  Tiles that one step reads exactly once (a sequence's
 // tokens after what the batch shares, in the cascade; every tile when the
