@@ -69,3 +69,32 @@ def test_fused_append_in_every_row(d, hq, hkv):
         assert np.array_equal(k, wk) and np.array_equal(v, wv)
         rep = compare(out, decode_workload(replace(w, k_pool=wk, v_pool=wv))[0])
         assert rep.passed, f"S={S}: {rep}"
+
+
+def test_sharing_changes_the_cache_policy_and_no_bit():
+    """A pool of more than 256 MB in use: streaming loads while few references
+    are to shared blocks, the default policy once most are."""
+    from types import SimpleNamespace
+    from paper_2510_14126_amd import binding
+    from paper_2510_14126_amd.device import PagedBatch
+    print("[gpu case] cache policy over a 275 MB pool with 10 shared blocks, then all shared", flush=True)
+    hkv, d, n = 8, 128, 1050
+    nb = 4 * n + 8
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    k, v = (torch.randn((nb, hkv, 16, d), generator=gen, dtype=torch.bfloat16, device="cuda:0") for _ in range(2))
+    tables = np.random.default_rng(6).permutation(nb)[: 4 * n].reshape(4, n).astype(np.int32)
+    tables[:, :10] = tables[0, :10]
+    w = SimpleNamespace(batch=4, num_q_heads=32, num_kv_heads=hkv, head_dim=d, num_blocks=nb,
+                        context_lens=np.array([16 * n, 16 * n - 5, 9000, 33], np.int32), block_tables=tables,
+                        scale=d ** -0.5, partition_size=512, max_context_len=16 * n,
+                        q=f32_to_bf16_bits(np.random.default_rng(7).standard_normal((4, 32, d), dtype=np.float32)))
+    pb = PagedBatch(w, "cuda:0", k_pool=k, v_pool=v)
+    pb.run()
+    torch.cuda.synchronize()
+    streamed = pb.out_bits().copy()
+    binding.kv_pool_retain(pb.pool, np.unique(tables[0]).tolist())
+    pb.out.fill_(0x7FC0)
+    pb.run()
+    torch.cuda.synchronize()
+    assert np.array_equal(streamed, pb.out_bits())
+    pb.close()
