@@ -1074,7 +1074,6 @@ int paged_attn_extend(const pa_kv_pool* pool, const void* q, const int32_t* q_st
   p.max_ctx = max_context_len;
   p.max_chunk = max_chunk;
   p.total_q = total_q;
-  p.groups = (int32_t)groups;
   p.scale_log2 = scale * 1.4426950408889634f;
   hipError_t e = pa::launch_extend(p, group, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail(PA_EHIP, "%s: kernel launch failed: %s", fn, hipGetErrorString(e));

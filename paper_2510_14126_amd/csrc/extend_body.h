@@ -48,6 +48,7 @@
 #include "kernels.h"
 #include "mfma_body.h"
 #include "pa_device.h"
+#include "shared_body.h"
 
 namespace pa {
 namespace extend {
@@ -92,6 +93,22 @@ __device__ __forceinline__ int v_off(int r, int c) {
   return r * (2 * kD) + (((c >> 1) ^ ((r & 3) << 1)) << 5) + ((c & 1) << 4);
 }
 
+// Sequence b's chunk: its first row in q and out, its length, and the
+// position of its first token.  Device data, clamped into the buffers.
+struct Chunk {
+  int start, len, first;
+};
+__device__ __forceinline__ Chunk chunk_of(const ExtendParams& p, int b) {
+  int ctx = p.context_lens[b];
+  ctx = ctx < 0 ? 0 : (ctx > p.max_ctx ? p.max_ctx : ctx);
+  int qs = p.q_start[b];
+  int L = p.q_start[b + 1] - qs;
+  qs = qs < 0 ? 0 : qs;
+  L = L < 0 ? 0 : (L > ctx ? ctx : (L > p.max_chunk ? p.max_chunk : L));
+  L = qs + L > p.total_q ? (p.total_q > qs ? p.total_q - qs : 0) : L;
+  return {qs, L, ctx - L};
+}
+
 template <int G>
 __device__ __forceinline__ void extend_body(const ExtendParams& p, int wg_index, lds_u8_t* smem) {
   const int lane = threadIdx.x & 63;
@@ -105,17 +122,12 @@ __device__ __forceinline__ void extend_body(const ExtendParams& p, int wg_index,
   const int grp = wg % p.groups;
   const int b = wg / p.groups;
 
-  int ctx = p.context_lens[b];
-  ctx = ctx < 0 ? 0 : (ctx > p.max_ctx ? p.max_ctx : ctx);
-  int qs = p.q_start[b];
-  int L = p.q_start[b + 1] - qs;
-  qs = qs < 0 ? 0 : qs;
-  L = L < 0 ? 0 : (L > ctx ? ctx : (L > p.max_chunk ? p.max_chunk : L));
-  L = qs + L > p.total_q ? (p.total_q > qs ? p.total_q - qs : 0) : L;
-  const int rows = L * G;
+  const Chunk c = chunk_of(p, b);
+  const int rows = c.len * G;
   if (grp * kExtendRowsPerWg >= rows) return;            // whole workgroup: no rows here
   const int row0 = grp * kExtendRowsPerWg + kRows * wave;   // this wavefront's first row
-  const int first = ctx - L;                             // position of chunk token 0
+  const int first = c.first;
+  const int qs = c.start;
 
   // Tokens the workgroup needs: up to its last row's position.
   const int last_row = min(rows, (grp + 1) * kExtendRowsPerWg) - 1;
@@ -387,6 +399,61 @@ __device__ __forceinline__ void extend_body(const ExtendParams& p, int wg_index,
       *reinterpret_cast<u32x4_t*>(p.out + ((size_t)(qs + R / G) * p.num_q_heads + g * G + R % G) * kD +
                                   (lane & 15) * 8) = x;
   }
+}
+
+// The form for small grids: 32 rows per workgroup with the tokens split over
+// the wavefronts (shared_body.h), a chain four times shorter per workgroup.
+constexpr int kSplitIdOffset = shared::kLdsBytes;
+constexpr int kSplitLdsBytes = kSplitIdOffset + kExtendMaxTokens / 16 * 4;
+
+template <int G>
+__device__ __forceinline__ void extend_split_body(const ExtendParams& p, int wg_index, lds_u8_t* smem) {
+  constexpr int kTile = shared::kRows;
+  const int n = threadIdx.x & 31;
+  int wg = wg_index;
+  const int g = wg % p.num_kv_heads;
+  wg /= p.num_kv_heads;
+  const int tile = wg % p.groups;
+  const int b = wg / p.groups;
+  const Chunk c = chunk_of(p, b);
+  const int rows = c.len * G;
+  const int row0 = tile * kTile;
+  if (row0 >= rows) return;                                // whole workgroup: no rows here
+  const int vis_max = c.first + (min(rows, row0 + kTile) - 1) / G + 1;   // tokens the tile needs
+  const int nblk = (vis_max + 15) >> 4;
+
+  lds_i32_t* ids = reinterpret_cast<lds_i32_t*>(smem + kSplitIdOffset);
+  {
+    const int32_t* bt = p.block_tables + (size_t)b * p.bt_stride;
+    for (int j = threadIdx.x; j < nblk; j += 64 * kWaves)
+      ids[j] = min(max(bt[j], 0), p.num_blocks - 1);
+    __syncthreads();
+  }
+
+  // A column without a row repeats the tile's first, sees everything and is
+  // not written.
+  const bool has_row = row0 + n < rows;
+  const int R = has_row ? row0 + n : row0;
+  const int lim = has_row ? c.first + R / G + 1 : 0x7fffffff;
+  constexpr size_t kTileElems = 16 * kD;
+  const size_t blk_stride = (size_t)p.num_kv_heads * kTileElems;
+  shared::tile_core(
+      p.q + ((size_t)(c.start + R / G) * p.num_q_heads + g * G + R % G) * kD, p.k_pool + (size_t)g * kTileElems,
+      p.v_pool + (size_t)g * kTileElems, nblk, p.scale_log2, smem,
+      [&](const uint16_t* base, int i) {   // rows past the last visible token are read as zeros
+        const size_t id = (size_t)__builtin_amdgcn_readfirstlane(ids[i]);
+        const int bytes = wave_uniform(min(16, vis_max - 16 * i) * (kD * 2));
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base + id * blk_stride), 0, bytes,
+                                                 kBufferDescWord3);
+      },
+      [&](int i) { return lim - 16 * i; }, [](int) {}, [](float, float) {},
+      [&](int r, int col, const mfma::floatx4_t& acc) {
+        const int row = row0 + r;
+        if (row < rows)
+          *reinterpret_cast<uint2*>(p.out + ((size_t)(c.start + row / G) * p.num_q_heads + g * G + row % G) * kD +
+                                    4 * col) =
+              make_uint2(bf16_rne(acc[0]) | (bf16_rne(acc[1]) << 16), bf16_rne(acc[2]) | (bf16_rne(acc[3]) << 16));
+      });
 }
 
 }  // namespace extend

@@ -162,7 +162,7 @@ struct ExtendParams {
   int32_t max_ctx;               // bound of context_lens (at most kExtendMaxTokens)
   int32_t max_chunk;             // bound of the chunk lengths
   int32_t total_q;               // rows of q and out
-  int32_t groups;                // row groups per sequence in the grid
+  int32_t groups;                // row groups per sequence in the grid (set by the launcher)
   float scale_log2;
 };
 hipError_t launch_extend(const ExtendParams& p, int group, hipStream_t stream);

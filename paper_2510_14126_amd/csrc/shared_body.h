@@ -71,68 +71,44 @@ __device__ __forceinline__ int a_row(int i) {
   return 16 * (a >> 1) + 2 * (4 * (a & 1) + b) + h;
 }
 
-// Rows and tokens of one workgroup: rows row0 .. row0 + 31 of the span's rows
-// 0 .. total_rows-1; tokens start .. end-1 (whole blocks), whose block ids
-// begin at bt; the result goes to partial slot `part`; the walk over the
-// blocks starts at block `rot`.
-struct Span {
-  int seq0, total_rows, row0;
-  int start, end;
-  const int32_t* bt;
-  int part;
-  int rot;
-};
-
-template <int G, bool TRACE>
-__device__ __forceinline__ void span_body(const PrefixParams& p, int g, const Span& sp, lds_u8_t* smem,
-                                          int32_t* trace) {
+// The rows of one tile against nblk blocks, on all wavefronts of the workgroup.
+//   q_row    query row (128 bf16) of column n
+//   desc(base, i)  buffer descriptor of the tile at block i (i < nblk) of the
+//            pool that starts at base (this KV head's tiles)
+//   vis(i)   tokens of block i that column n sees (may exceed 16 or be
+//            negative)
+//   seen(i)  called once per block by the wavefront that loads it
+//   stats(mx, lt)  maximum (log2 units) and sum of column n's row, once per
+//            workgroup on wavefront 0 (both half wavefronts hold them)
+//   put(row, c, acc)  dims 4c .. 4c+3 of the normalised output of a tile row
+// A block that column n does not see, or a token past its vis, gets weight 0:
+// its V must be finite or read as zero.
+template <typename Desc, typename Vis, typename Seen, typename Stats, typename Put>
+__device__ __forceinline__ void tile_core(const uint16_t* q_row, const uint16_t* kbase, const uint16_t* vbase,
+                                          int nblk, float scale_log2, lds_u8_t* smem, Desc&& desc, Vis&& vis,
+                                          Seen&& seen, Stats&& stats, Put&& put) {
   const int lane = threadIdx.x & 63;
   const int wave = wave_uniform(threadIdx.x >> 6);
   const int h = lane >> 5;
   const int n = lane & 31;
 
-  const int nblk = (sp.end - sp.start) >> 4;    // 1 .. 64 for every launched span
-  const int raw = lane < nblk ? sp.bt[lane] : 0;
-  const int idc = min(max(raw, 0), p.num_blocks - 1);
-
-  // Column n is row R = row0 + n.  A negative scale goes into the sign of Q
-  // (bf16 negation is exact, and so is the negation of every score).
-  const int R = sp.row0 + n;
-  const bool has_row = R < sp.total_rows;
-  const int bR = has_row ? sp.seq0 + R / G : sp.seq0;
-  const size_t qrow_index = (size_t)bR * p.num_q_heads + g * G + (has_row ? R % G : 0);
-  const uint32_t qflip = p.scale_log2 < 0.f ? 0x80008000u : 0u;
-  // A scale of zero becomes the smallest normal number, so that masked scores
-  // stay -inf times it (scores below 2^100 still weigh exactly the same).
-  const float scale = p.scale_log2 == 0.f ? 1.1754944e-38f : fabsf(p.scale_log2);
+  // A negative scale goes into the sign of Q (bf16 negation is exact, and so
+  // is the negation of every score).  A scale of zero becomes the smallest
+  // normal number, so that masked scores stay -inf times it (scores below
+  // 2^100 still weigh exactly the same).
+  const uint32_t qflip = scale_log2 < 0.f ? 0x80008000u : 0u;
+  const float scale = scale_log2 == 0.f ? 1.1754944e-38f : fabsf(scale_log2);
   u32x4_t qb[8];
-  {
-    const uint16_t* qrow = p.q + qrow_index * kD;
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const uint4 w = *reinterpret_cast<const uint4*>(qrow + (2 * s + h) * 8);
-      qb[s] = u32x4_t{w.x ^ qflip, w.y ^ qflip, w.z ^ qflip, w.w ^ qflip};
-    }
+  for (int s = 0; s < 8; ++s) {
+    const uint4 w = *reinterpret_cast<const uint4*>(q_row + (2 * s + h) * 8);
+    qb[s] = u32x4_t{w.x ^ qflip, w.y ^ qflip, w.z ^ qflip, w.w ^ qflip};
   }
-  // Tokens column n sees; a column without a row repeats the first one's
-  // query, sees everything and is not written.
-  int lim = p.context_lens[bR];
-  lim = !has_row ? 0x7fffffff : (lim < 0 ? 0 : (lim > p.max_ctx ? p.max_ctx : lim));
 
-  constexpr size_t kTileElems = 16 * kD;
-  const size_t blk_stride = (size_t)p.num_kv_heads * kTileElems;
-  const uint16_t* kbase = p.k_pool + (size_t)g * kTileElems;
-  const uint16_t* vbase = p.v_pool + (size_t)g * kTileElems;
   const int nstage = (nblk + 1) >> 1;
-  auto block_of = [&](int i) { const int j = i + sp.rot; return j >= nblk ? j - nblk : j; };
-  // Tile of the walk's block i; past the last block an empty descriptor (the
-  // loads return zeros).
-  auto tile = [&](const uint16_t* base, int i) {
-    const bool ok = i < nblk;
-    const size_t id = (size_t)__builtin_amdgcn_readlane(idc, ok ? block_of(i) : 0);
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base + id * blk_stride), 0,
-                                             ok ? (int)(kTileElems * 2) : 0, kBufferDescWord3);
-  };
+  // Past the last block the descriptor is empty: the loads return zeros.
+  const __amdgpu_buffer_rsrc_t none =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(kbase), 0, 0, kBufferDescWord3);
   const int krow = lane >> 4, kchunk = lane & 15;      // rows 4u + krow
   const int k_lane = (krow * kD + kchunk * 8) * 2;
   const int v_lane = (h * kD + n * 4) * 2;             // rows 2u + h, dims 4n ..
@@ -141,7 +117,7 @@ __device__ __forceinline__ void span_body(const PrefixParams& p, int g, const Sp
   auto load_k = [&](int s) {
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
-      const __amdgpu_buffer_rsrc_t d = tile(kbase, 2 * s + m);
+      const __amdgpu_buffer_rsrc_t d = 2 * s + m < nblk ? desc(kbase, 2 * s + m) : none;
 #pragma unroll
       for (int u = 0; u < 4; ++u)
         rk[m][u] = __builtin_bit_cast(u32x4_t,
@@ -151,7 +127,7 @@ __device__ __forceinline__ void span_body(const PrefixParams& p, int g, const Sp
   auto load_v = [&](int s) {
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
-      const __amdgpu_buffer_rsrc_t d = tile(vbase, 2 * s + m);
+      const __amdgpu_buffer_rsrc_t d = 2 * s + m < nblk ? desc(vbase, 2 * s + m) : none;
 #pragma unroll
       for (int u = 0; u < 8; ++u)
         rv[m][u] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(d, v_lane + u * 2 * kD * 2, 0, 0));
@@ -203,29 +179,17 @@ __device__ __forceinline__ void span_body(const PrefixParams& p, int g, const Sp
           __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const lds_u32x4_t*>(stage + k_off(arow, 2 * c + h))),
           __builtin_bit_cast(bf16x8_t, qb[c]), a, 0, 0, 0);
 
-    // Tokens of each block that column n sees (register r = 8 mb + e: token
-    // 2e + h).
-    int vis[2];
+    // Register r = 8 mb + e is token 2e + h of block 2s + mb.
+    int see[2];
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb) {
-      const int i = 2 * s + mb;
-      const int b = i < nblk ? block_of(i) : 0;
-      vis[mb] = i < nblk ? lim - (sp.start + 16 * b) : 0;
-      if constexpr (TRACE) {
-        // slot = the block's position in the span (not in the walk)
-        const int id = __builtin_amdgcn_readlane(raw, b);
-        if (i < nblk && lane == 0) {
-          int32_t* tr = trace + 3 * b;
-          tr[0] = (sp.start >> 4) + b;
-          tr[1] = id;
-          tr[2] = 16;
-        }
-      }
+      see[mb] = 2 * s + mb < nblk ? vis(2 * s + mb) : 0;
+      if (2 * s + mb < nblk) seen(2 * s + mb);
     }
-    if (__builtin_amdgcn_ballot_w64(min(vis[0], vis[1]) < 16) != 0) {
+    if (__builtin_amdgcn_ballot_w64(min(see[0], see[1]) < 16) != 0) {
 #pragma unroll
       for (int r = 0; r < 16; ++r)
-        if (2 * (r & 7) + h >= vis[r >> 3]) a[r] = -__builtin_inff();
+        if (2 * (r & 7) + h >= see[r >> 3]) a[r] = -__builtin_inff();
     }
 
     // The rescale test needs no cross-lane reduction: any lane above its
@@ -317,8 +281,7 @@ __device__ __forceinline__ void span_body(const PrefixParams& p, int g, const Sp
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) lt = fmaf(sl[w * kRows + n], fast_exp2(sm[w * kRows + n] - mref), lt);
   const float inv = lt > 0.f ? 1.0f / lt : 0.f;
-  if (wave == 0 && h == 0 && has_row)
-    p.part_lse[qrow_index * p.part_stride + sp.part] = lt > 0.f ? (mx + log2f(lt)) * kLn2 : -__builtin_inff();
+  if (wave == 0) stats(mx, lt);
   float f[16];
   per_row(fast_exp2(m - mref) * inv, f);
   auto piece = [&](int d, int b) {   // the lane's dims of row 8d + 4h + b, normalised
@@ -344,13 +307,77 @@ __device__ __forceinline__ void span_body(const PrefixParams& p, int g, const Sp
 #pragma unroll
         for (int w = 0; w < kWaves; ++w)
           acc += w == d ? piece(d, b) : *reinterpret_cast<const lds_floatx4_t*>(slot(d, w) + b * 1024);
-        const int row = sp.row0 + 8 * d + 4 * h + b;
-        if (row < sp.total_rows) {
-          const size_t at = ((size_t)(sp.seq0 + row / G) * p.num_q_heads + g * G + row % G) * p.part_stride + sp.part;
-          store_partial4(p.part_o + at * kD + 4 * n, acc[0], acc[1], acc[2], acc[3]);
-        }
+        put(8 * d + 4 * h + b, n, acc);
       }
     }
+}
+
+// Rows and tokens of one workgroup: rows row0 .. row0 + 31 of the span's rows
+// 0 .. total_rows-1; tokens start .. end-1 (whole blocks), whose block ids
+// begin at bt; the result goes to partial slot `part`; the walk over the
+// blocks starts at block `rot`.
+struct Span {
+  int seq0, total_rows, row0;
+  int start, end;
+  const int32_t* bt;
+  int part;
+  int rot;
+};
+
+template <int G, bool TRACE>
+__device__ __forceinline__ void span_body(const PrefixParams& p, int g, const Span& sp, lds_u8_t* smem,
+                                          int32_t* trace) {
+  const int lane = threadIdx.x & 63;
+  const int n = lane & 31;
+  const int nblk = (sp.end - sp.start) >> 4;    // 1 .. 64 for every launched span
+  const int raw = lane < nblk ? sp.bt[lane] : 0;
+  const int idc = min(max(raw, 0), p.num_blocks - 1);
+
+  // Column n is row R = row0 + n.  A column without a row repeats the first
+  // one's query, sees everything and is not written.
+  const int R = sp.row0 + n;
+  const bool has_row = R < sp.total_rows;
+  const int bR = has_row ? sp.seq0 + R / G : sp.seq0;
+  const size_t q_index = (size_t)bR * p.num_q_heads + g * G + (has_row ? R % G : 0);
+  int lim = p.context_lens[bR];
+  lim = !has_row ? 0x7fffffff : (lim < 0 ? 0 : (lim > p.max_ctx ? p.max_ctx : lim));
+
+  constexpr size_t kTileElems = 16 * kD;
+  const size_t blk_stride = (size_t)p.num_kv_heads * kTileElems;
+  auto block_of = [&](int i) { const int j = i + sp.rot; return j >= nblk ? j - nblk : j; };
+  tile_core(
+      p.q + q_index * kD, p.k_pool + (size_t)g * kTileElems, p.v_pool + (size_t)g * kTileElems, nblk,
+      p.scale_log2, smem,
+      [&](const uint16_t* base, int i) {
+        const size_t id = (size_t)__builtin_amdgcn_readlane(idc, block_of(i));
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base + id * blk_stride), 0,
+                                                 (int)(kTileElems * 2), kBufferDescWord3);
+      },
+      [&](int i) { return lim - (sp.start + 16 * block_of(i)); },
+      [&](int i) {
+        if constexpr (TRACE) {
+          // slot = the block's position in the span (not in the walk)
+          const int b = block_of(i);
+          const int id = __builtin_amdgcn_readlane(raw, b);
+          if (lane == 0) {
+            int32_t* tr = trace + 3 * b;
+            tr[0] = (sp.start >> 4) + b;
+            tr[1] = id;
+            tr[2] = 16;
+          }
+        }
+      },
+      [&](float mx, float lt) {
+        if (lane < kRows && has_row)
+          p.part_lse[q_index * p.part_stride + sp.part] = lt > 0.f ? (mx + log2f(lt)) * kLn2 : -__builtin_inff();
+      },
+      [&](int r, int c, const floatx4_t& acc) {
+        const int row = sp.row0 + r;
+        if (row < sp.total_rows) {
+          const size_t at = ((size_t)(sp.seq0 + row / G) * p.num_q_heads + g * G + row % G) * p.part_stride + sp.part;
+          store_partial4(p.part_o + at * kD + 4 * c, acc[0], acc[1], acc[2], acc[3]);
+        }
+      });
 }
 
 // The batch-wide prefix: partition `part` of the prefix against row tile

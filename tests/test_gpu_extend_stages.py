@@ -1,5 +1,6 @@
-"""Chunked prefill at the edges of its 32-token stages, its three LDS slots,
-its 32-row wavefront tiles and 128-row workgroups: contexts and chunks around
+"""Chunked prefill, in both of its forms (the grid's size decides), at the
+edges of its 32-token stages, its three LDS slots, its 32-row tiles and
+128-row workgroups: contexts and chunks around
 multiples of them, chunks that start inside a stage and inside a block, one,
 two, three and eight KV heads.  Poison past every context; every output row
 against the oracle under the parity gate."""
@@ -19,6 +20,8 @@ CASES = [
     ([63, 64, 65, 95, 96, 97, 127, 128, 129], [63, 1, 65, 9, 32, 31, 127, 128, 33]),
     ([191, 192, 193, 287, 288, 289, 400], [1, 17, 193, 15, 16, 65, 64]),
     ([700, 1056, 640], [33, 1, 129]),
+    # large enough a grid for the 128-row form at 64 heads over 8
+    ([129, 96, 31, 64, 65, 200, 192, 33, 97, 1], [129, 64, 31, 63, 65, 100, 97, 32, 96, 1]),
 ]
 
 
