@@ -19,7 +19,7 @@ namespace {
 
 constexpr int kMax(int a, int b) { return a > b ? a : b; }
 template <int G, bool SPLIT>
-constexpr int cascade_lds() { return kMax(SPLIT ? shared::kLdsBytes : mfma::kPrefixLdsBytes, decode::lds_bytes<128, G>()); }
+constexpr int cascade_lds() { return kMax(SPLIT ? shared::kLdsBytes : mfma::kPrefixLdsBytes, decode::lds_bytes<128, G, true>()); }
 
 // Tiles in flight per wavefront of the per-sequence half: two for the short
 // tails of the G = 4 stages, three for the 512-token items of G = 8.  (Four

@@ -226,21 +226,35 @@ __device__ __forceinline__ void process_tile(WaveState<D>& S, const KvTile<D>& T
   }
 }
 
+// Whether a workgroup may take a second sequence's rows in the columns that
+// four query heads leave idle: where sequences may share blocks.
+template <int G, bool STREAM>
+constexpr bool pairs() { return G == 4 && !STREAM; }
+
 // LDS of one work item: a staged K tile per wavefront, reused by the merge
-// ([wave][G] maxima and sums, then [wave][G][D] outputs).
-template <int D, int G>
+// ([wave][rows] maxima and sums, then [wave][rows][D] outputs).
+template <int D, int G, bool STREAM>
 constexpr int lds_bytes() {
+  constexpr int rows = pairs<G, STREAM>() ? 2 * G : G;
   const int stage = kWaves * 16 * D * 2;
-  const int merge = (2 * kWaves * G + kWaves * G * D) * 4;
+  const int merge = (2 * kWaves * rows + kWaves * rows * D) * 4;
   return stage > merge ? stage : merge;
 }
 
 // One work item (partition, sequence, KV head) = workgroup `wg_index`;
-// `smem` points at lds_bytes<D, G>() bytes of LDS.  STREAM: load the tiles as
-// streaming data (kLoadStreaming); it changes caching, never the results.
-// APPEND: the fused KV append (DecodeParams::k_new): the item that holds
-// token ctx - 1 takes its K and V rows from k_new / v_new in registers
-// (whatever the pool slot holds) and stores them into the slot.
+// `smem` points at lds_bytes<D, G, STREAM>() bytes of LDS.  STREAM: load the
+// tiles as streaming data (kLoadStreaming); it changes caching, never the
+// results.
+//
+// Pairs: with four query heads, columns 8..15 of a tile are idle.  Where blocks
+// may be shared (!STREAM), the workgroups of sequences 2k and 2k+1 compare the
+// partition's block ids of both; if both contexts hold the whole partition and
+// every id is equal, one of them computes both sequences' rows at the cost of
+// one, and the other leaves.  Columns do not affect each other, so the
+// partials have the same bits either way.  (64 sequences over a shared
+// 2048-token prefix, 512-token partitions, no cascade: 42.7 -> 33.6 us a step;
+// with the even sequence always computing, no change: half of the shader
+// engines had all the work.)
 template <int D, int G, int NBUF, bool TRACE, bool STREAM, bool APPEND>
 __device__ __forceinline__ void decode_body(const DecodeParams& p, int wg_index, lds_u8_t* smem) {
   constexpr int VW = D / 32;
@@ -262,14 +276,23 @@ __device__ __forceinline__ void decode_body(const DecodeParams& p, int wg_index,
   // The first 64 block ids and the query rows are loaded before the context
   // length arrives (j0 < bt_stride for every launched partition).
   const int raw_first = lane < min(64, p.bt_stride - j0) ? bt[lane] : 0;
+  constexpr bool PAIR = pairs<G, STREAM>();
+  const int b2 = (b ^ 1) < p.batch ? b ^ 1 : b;   // the sequence to pair with
+  int raw_second = 0;
+  if constexpr (PAIR) {
+    const int32_t* bt2 = p.block_tables + (size_t)b2 * p.bt_stride + j0;
+    raw_second = lane < min(64, p.bt_stride - j0) ? bt2[lane] : 0;
+  }
 
-  // Q^T operand: column n holds query row n % G; dims 32s + 8q .. +8.  bf16
-  // negation is exact, and so is the negation of every score.
+  // Q^T operand: column n holds query row n % G (PAIR: columns 8..15 those of
+  // b2); dims 32s + 8q .. +8.  bf16 negation is exact, and so is the negation
+  // of every score.
   const uint32_t qflip = p.scale_log2 < 0.f ? 0x80008000u : 0u;
   const float scale_abs = fabsf(p.scale_log2);
   uint4 qb[D / 32];
   {
-    const uint16_t* qrow = p.q + ((size_t)b * p.num_q_heads + h0 + (n & (G - 1))) * D;
+    const int bq = PAIR && n >= 8 ? b2 : b;
+    const uint16_t* qrow = p.q + ((size_t)bq * p.num_q_heads + h0 + (n & (G - 1))) * D;
 #pragma unroll
     for (int s = 0; s < D / 32; ++s) {
       uint4 w = *reinterpret_cast<const uint4*>(qrow + (4 * s + q) * 8);
@@ -282,6 +305,19 @@ __device__ __forceinline__ void decode_body(const DecodeParams& p, int wg_index,
   ctx = ctx < 0 ? 0 : (ctx > p.max_ctx ? p.max_ctx : ctx);
   const bool split = p.write_partials != 0;
   if (split && start >= ctx) return;  // whole workgroup; the reduce skips this partition
+  bool paired = false;
+  if constexpr (PAIR) {
+    // Tokens both contexts must hold; with the fused append, the new tokens
+    // must lie past them.
+    const int need = start + p.part_tokens + (APPEND ? 1 : 0);
+    const int blocks = p.part_tokens >> 4;
+    paired = split && b2 != b && blocks <= 64 && ctx >= need && min(p.context_lens[b2], p.max_ctx) >= need &&
+             __builtin_amdgcn_ballot_w64(lane < blocks && raw_first != raw_second) == 0;
+    // Whole workgroup: computed with sequence b2.  Which of the two computes
+    // alternates, so that every shader engine of an XCD gets some of the work
+    // (consecutive sequences go to them in a fixed cycle of four).
+    if (paired && (b & 1) != ((b >> 2) & 1)) return;
+  }
   const int end = min(ctx, start + p.part_tokens);
   const int nblk = end > start ? (end - start + 15) >> 4 : 0;
 
@@ -358,6 +394,12 @@ __device__ __forceinline__ void decode_body(const DecodeParams& p, int wg_index,
           tr[0] = j0 + c0 + i;
           tr[1] = __builtin_amdgcn_readlane(raw, i);
           tr[2] = valid;
+          if (PAIR && paired) {   // the same tiles of sequence b2
+            int32_t* tr2 = tr + (int64_t)(b2 - b) * p.num_kv_heads * p.trace_tiles * 3;
+            tr2[0] = tr[0];
+            tr2[1] = tr[1];
+            tr2[2] = valid;
+          }
         }
       }
     };
@@ -417,20 +459,25 @@ __device__ __forceinline__ void decode_body(const DecodeParams& p, int wg_index,
       if constexpr (G == 8) swap32(x, y); else swap16(x, y);
       sum[j][r] = x + y;
     }
+  constexpr int kMergeRows = PAIR ? 2 * G : G;
   const int half = G == 8 ? q >> 1 : q & 1;          // which half of the lane's dims
-  const int qrow = G == 8 ? q & 1 : 0;               // rows 4 * qrow + r
-  const bool keeps = G == 8 || q < 2;                // G = 4: groups 2 and 3 hold copies
+  const int qrow = G == 8 ? q & 1 : q >> 1;          // merge rows 4 * qrow + r
+  const bool keeps = G == 8 || PAIR || q < 2;        // else groups 2 and 3 hold copies
 
   // Merge the wavefronts through LDS (the staging area is free now).
   __syncthreads();
-  lds_f32_t* sm = reinterpret_cast<lds_f32_t*>(smem);       // [kWaves][G]
-  lds_f32_t* sl = sm + kWaves * G;                           // [kWaves][G]
-  lds_f32_t* sacc = sl + kWaves * G;                         // [kWaves][G][D]
-  if (q == 0 && n < G) { sm[wave * G + n] = S.m; sl[wave * G + n] = lrow; }
+  lds_f32_t* sm = reinterpret_cast<lds_f32_t*>(smem);       // [kWaves][rows]
+  lds_f32_t* sl = sm + kWaves * kMergeRows;                  // [kWaves][rows]
+  lds_f32_t* sacc = sl + kWaves * kMergeRows;                // [kWaves][rows][D]
+  if (q == 0 && (n & 7) < G && (PAIR || n < 8)) {
+    const int r = PAIR && n >= 8 ? n - 8 + G : n;
+    sm[wave * kMergeRows + r] = S.m;
+    sl[wave * kMergeRows + r] = lrow;
+  }
   if (keeps) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      lds_f32_t* row = sacc + (wave * G + 4 * qrow + r) * D + DPL * n + (DPL / 2) * half;
+      lds_f32_t* row = sacc + (wave * kMergeRows + 4 * qrow + r) * D + DPL * n + (DPL / 2) * half;
       if constexpr (D == 128) {
         *reinterpret_cast<lds_floatx4_t*>(row) = floatx4_t{sum[0][r], sum[1][r], sum[2][r], sum[3][r]};
       } else {
@@ -449,25 +496,26 @@ __device__ __forceinline__ void decode_body(const DecodeParams& p, int wg_index,
   constexpr int kRowThreads = D / 2;
   constexpr int kRowsPerPass = 64 * kWaves / kRowThreads;
   const int d = 2 * (threadIdx.x % kRowThreads);
+  const int rows = PAIR && paired ? 2 * G : G;
 #pragma unroll
-  for (int r0 = 0; r0 < G; r0 += kRowsPerPass) {
+  for (int r0 = 0; r0 < kMergeRows; r0 += kRowsPerPass) {
     const int r = r0 + threadIdx.x / kRowThreads;
-    if (kRowsPerPass > G && r >= G) return;
+    if (r >= rows) return;
     float mx = sm[r];
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) mx = fmaxf(mx, sm[w * G + r]);
+    for (int w = 1; w < kWaves; ++w) mx = fmaxf(mx, sm[w * kMergeRows + r]);
     const float mref = (mx == -__builtin_inff()) ? 0.f : mx;
     float lt = 0.f, o0 = 0.f, o1 = 0.f;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-      const float f = fast_exp2(sm[w * G + r] - mref);
-      lt = fmaf(sl[w * G + r], f, lt);
-      const floatx2_t a = *reinterpret_cast<const lds_floatx2_t*>(sacc + (w * G + r) * D + d);
+      const float f = fast_exp2(sm[w * kMergeRows + r] - mref);
+      lt = fmaf(sl[w * kMergeRows + r], f, lt);
+      const floatx2_t a = *reinterpret_cast<const lds_floatx2_t*>(sacc + (w * kMergeRows + r) * D + d);
       o0 = fmaf(a[0], f, o0);
       o1 = fmaf(a[1], f, o1);
     }
     const float inv = lt > 0.f ? 1.0f / lt : 0.f;
-    const size_t orow = (size_t)b * p.num_q_heads + h0 + r;
+    const size_t orow = (size_t)(PAIR && r >= G ? b2 : b) * p.num_q_heads + h0 + r % G;
     if (!split) {
       *reinterpret_cast<uint32_t*>(p.out + orow * D + d) = bf16_rne(o0 * inv) | (bf16_rne(o1 * inv) << 16);
     } else {

@@ -23,7 +23,7 @@ constexpr int nbuf() { return D == 64 ? 4 : (STREAM ? 3 : 2); }
 template <int D, int G, bool TRACE, bool STREAM, bool APPEND>
 __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2, 8)))
 decode_mfma_kernel(const DecodeParams p) {
-  __shared__ __attribute__((aligned(16))) uint8_t smem[decode::lds_bytes<D, G>()];
+  __shared__ __attribute__((aligned(16))) uint8_t smem[decode::lds_bytes<D, G, STREAM>()];
   decode::decode_body<D, G, nbuf<D, STREAM>(), TRACE, STREAM, APPEND>(p, blockIdx.x, (lds_u8_t*)smem);
 }
 

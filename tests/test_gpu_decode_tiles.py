@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 from oracle import compare, decode_workload  # noqa: E402
-from workloads import f32_to_bf16_bits, logical_case, page_case  # noqa: E402
+from workloads import duplicate_shared_blocks, f32_to_bf16_bits, logical_case, page_case  # noqa: E402
 
 CTX = [0, 1, 15, 16, 17, 33, 48, 63, 64, 65, 81, 127, 1009, 1023, 1024, 1025, 1041, 2064, 2100]
 
@@ -98,3 +98,41 @@ def test_sharing_changes_the_cache_policy_and_no_bit():
     torch.cuda.synchronize()
     assert np.array_equal(streamed, pb.out_bits())
     pb.close()
+
+
+@pytest.mark.parametrize("S", [16, 64, 176, 1024])
+@pytest.mark.parametrize("d,hq,hkv", [(64, 8, 2), (128, 12, 3), (128, 8, 1)])
+def test_pairs_of_sequences_over_shared_blocks(d, hq, hkv, S):
+    """Neighbouring sequences whose partitions hold the same blocks (four query
+    heads: computed together) give the same bits as over private copies: shared
+    prefixes that end inside a partition, an odd batch, contexts that end
+    inside, at and one past the shared tokens, and the fused append."""
+    prefix = 1056
+    ctx = [prefix, prefix + 1, 1500, 1500, 1088, 3000, prefix + 16, 2112, 1100]
+    print(f"[gpu case] pairs over shared blocks D={d} Hq={hq} Hkv={hkv} S={S}", flush=True)
+    w = page_case(logical_case(440 + d + hq, len(ctx), hq, hkv, d, ctx, prefix_len=prefix), 441, poison=True)
+    w.context_lens[2] = 700                # ends inside the shared tokens
+    own = duplicate_shared_blocks(w)
+    assert compare(run_step(w, S), decode_workload(w)[0]).passed
+    for schedule in (False, True):
+        assert np.array_equal(run_step(w, S, schedule), run_step(own, S, schedule))
+    # the appended token: sequences 0 and 2 end in shared blocks and are left out
+    rng = np.random.default_rng(442)
+    new = [torch.from_numpy(f32_to_bf16_bits(rng.standard_normal((len(ctx), hkv, d), dtype=np.float32))
+                            .view(np.int16)).cuda() for _ in range(2)]
+    w.context_lens[[0, 2]] = 0
+    own.context_lens[[0, 2]] = 0
+    assert np.array_equal(run_step(w, S, new=new), run_step(own, S, new=new))
+
+
+def run_step(w, S, schedule=False, new=None):
+    from paper_2510_14126_amd.device import PagedBatch
+    pb = PagedBatch(w, "cuda:0", partition_size=S, schedule=schedule)
+    pb.out.fill_(0x7FC0)
+    pb.decode_append(*new) if new else pb.decode()
+    if pb.needs_reduce:
+        pb.reduce()
+    torch.cuda.synchronize()
+    out = pb.out_bits()
+    pb.close()
+    return out
