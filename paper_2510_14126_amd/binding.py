@@ -1,4 +1,5 @@
-"""ctypes binding of ``libpaged_attn.so`` (argument marshalling only).
+"""Binding of ``libpaged_attn.so`` (argument marshalling only): ctypes, and for
+the functions a serving loop calls every step the native ``_pycall`` extension.
 
 Every function here has the name and argument order of the C function it
 calls; see ``include/paged_attn.h`` for meanings, layouts and ownership.
@@ -114,7 +115,19 @@ def _load(path: str = LIB_PATH) -> ctypes.CDLL:
     return lib
 
 
+def _load_pycall(lib: ctypes.CDLL):
+    """The native calls of the per-step functions, bound to ``lib``."""
+    try:
+        from . import _pycall
+    except ImportError as e:
+        raise ImportError("the _pycall extension is missing: build the library first "
+                          "(python -c 'import __graft_entry__ as g; g.build()')") from e
+    _pycall.bind({n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in _pycall.NAMES})
+    return _pycall
+
+
 _lib = _load()
+_pycall = _load_pycall(_lib)
 
 
 def library() -> ctypes.CDLL:
@@ -255,17 +268,17 @@ def paged_attn_workspace_size(batch, num_q_heads, head_dim, max_context_len, par
 def paged_attn_decode(pool: KVPool, q, block_tables, bt_stride, context_lens, batch, num_q_heads,
                       scale, max_context_len, partition_size, out, partial_out=None,
                       partial_lse=None, stream=None) -> None:
-    _check(_lib.paged_attn_decode(pool._handle(), _ptr(q), _ptr(block_tables), bt_stride,
-                                  _ptr(context_lens), batch, num_q_heads, scale, max_context_len,
-                                  partition_size, _ptr(out), _ptr(partial_out), _ptr(partial_lse),
-                                  _ptr(stream)))
+    _check(_pycall.paged_attn_decode(pool._handle(), q, block_tables, bt_stride,
+                                  context_lens, batch, num_q_heads, scale, max_context_len,
+                                  partition_size, out, partial_out, partial_lse,
+                                  stream))
 
 
 def paged_attn_reduce(partial_out, partial_lse, context_lens, batch, num_q_heads, head_dim,
                       partition_size, max_partitions, out, stream=None) -> None:
-    _check(_lib.paged_attn_reduce(_ptr(partial_out), _ptr(partial_lse), _ptr(context_lens), batch,
-                                  num_q_heads, head_dim, partition_size, max_partitions, _ptr(out),
-                                  _ptr(stream)))
+    _check(_pycall.paged_attn_reduce(partial_out, partial_lse, context_lens, batch,
+                                  num_q_heads, head_dim, partition_size, max_partitions, out,
+                                  stream))
 
 
 def paged_attn_decode_trace(pool: KVPool, q, block_tables, bt_stride, context_lens, batch,
@@ -291,17 +304,17 @@ def pa_gather_tiles(pool: KVPool, block_tables, bt_stride, batch, spans, num_spa
 
 def paged_attn_append_kv(pool: KVPool, k_new, v_new, block_tables, bt_stride, context_lens, batch,
                          stream=None) -> None:
-    _check(_lib.paged_attn_append_kv(pool._handle(), _ptr(k_new), _ptr(v_new), _ptr(block_tables),
-                                     bt_stride, _ptr(context_lens), batch, _ptr(stream)))
+    _check(_pycall.paged_attn_append_kv(pool._handle(), k_new, v_new, block_tables,
+                                     bt_stride, context_lens, batch, stream))
 
 
 def paged_attn_decode_append(pool: KVPool, q, k_new, v_new, block_tables, bt_stride, context_lens,
                              batch, num_q_heads, scale, max_context_len, partition_size, items,
                              num_items, out, partial_out=None, partial_lse=None, stream=None) -> None:
-    _check(_lib.paged_attn_decode_append(
-        pool._handle(), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(block_tables), bt_stride,
-        _ptr(context_lens), batch, num_q_heads, scale, max_context_len, partition_size, _ptr(items),
-        num_items, _ptr(out), _ptr(partial_out), _ptr(partial_lse), _ptr(stream)))
+    _check(_pycall.paged_attn_decode_append(
+        pool._handle(), q, k_new, v_new, block_tables, bt_stride,
+        context_lens, batch, num_q_heads, scale, max_context_len, partition_size, items,
+        num_items, out, partial_out, partial_lse, stream))
 
 
 def paged_attn_decode_cascade_append(pool: KVPool, q, k_new, v_new, block_tables, bt_stride,
@@ -309,11 +322,11 @@ def paged_attn_decode_cascade_append(pool: KVPool, q, k_new, v_new, block_tables
                                      partition_size, prefix_len, prefix_partition_size, group_start,
                                      num_groups, max_group_size, group_len, items, num_items,
                                      partial_out, partial_lse, stream=None) -> None:
-    _check(_lib.paged_attn_decode_cascade_append(
-        pool._handle(), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(block_tables), bt_stride,
-        _ptr(context_lens), batch, num_q_heads, scale, max_context_len, partition_size, prefix_len,
-        prefix_partition_size, _ptr(group_start), num_groups, max_group_size, group_len, _ptr(items),
-        num_items, _ptr(partial_out), _ptr(partial_lse), _ptr(stream)))
+    _check(_pycall.paged_attn_decode_cascade_append(
+        pool._handle(), q, k_new, v_new, block_tables, bt_stride,
+        context_lens, batch, num_q_heads, scale, max_context_len, partition_size, prefix_len,
+        prefix_partition_size, group_start, num_groups, max_group_size, group_len, items,
+        num_items, partial_out, partial_lse, stream))
 
 
 def paged_attn_cascade_workspace_size(batch, num_q_heads, head_dim, max_context_len,
@@ -330,11 +343,11 @@ def paged_attn_cascade_workspace_size(batch, num_q_heads, head_dim, max_context_
 def paged_attn_decode_cascade(pool: KVPool, q, block_tables, bt_stride, context_lens, batch,
                               num_q_heads, scale, max_context_len, partition_size, prefix_len,
                               prefix_partition_size, partial_out, partial_lse, stream=None) -> None:
-    _check(_lib.paged_attn_decode_cascade(pool._handle(), _ptr(q), _ptr(block_tables), bt_stride,
-                                          _ptr(context_lens), batch, num_q_heads, scale,
+    _check(_pycall.paged_attn_decode_cascade(pool._handle(), q, block_tables, bt_stride,
+                                          context_lens, batch, num_q_heads, scale,
                                           max_context_len, partition_size, prefix_len,
-                                          prefix_partition_size, _ptr(partial_out),
-                                          _ptr(partial_lse), _ptr(stream)))
+                                          prefix_partition_size, partial_out,
+                                          partial_lse, stream))
 
 
 def paged_attn_cascade_groups_workspace_size(batch, num_q_heads, head_dim, max_context_len,
@@ -353,36 +366,36 @@ def paged_attn_decode_cascade_groups(pool: KVPool, q, block_tables, bt_stride, c
                                      prefix_len, prefix_partition_size, group_start, num_groups,
                                      max_group_size, group_len, items, num_items, partial_out,
                                      partial_lse, stream=None) -> None:
-    _check(_lib.paged_attn_decode_cascade_groups(
-        pool._handle(), _ptr(q), _ptr(block_tables), bt_stride, _ptr(context_lens), batch,
+    _check(_pycall.paged_attn_decode_cascade_groups(
+        pool._handle(), q, block_tables, bt_stride, context_lens, batch,
         num_q_heads, scale, max_context_len, partition_size, prefix_len, prefix_partition_size,
-        _ptr(group_start), num_groups, max_group_size, group_len, _ptr(items), num_items,
-        _ptr(partial_out), _ptr(partial_lse), _ptr(stream)))
+        group_start, num_groups, max_group_size, group_len, items, num_items,
+        partial_out, partial_lse, stream))
 
 
 def paged_attn_reduce_cascade_groups(partial_out, partial_lse, context_lens, batch, num_q_heads,
                                      head_dim, partition_size, prefix_len, prefix_partition_size,
                                      group_len, max_partitions, out, stream=None) -> None:
-    _check(_lib.paged_attn_reduce_cascade_groups(
-        _ptr(partial_out), _ptr(partial_lse), _ptr(context_lens), batch, num_q_heads, head_dim,
-        partition_size, prefix_len, prefix_partition_size, group_len, max_partitions, _ptr(out),
-        _ptr(stream)))
+    _check(_pycall.paged_attn_reduce_cascade_groups(
+        partial_out, partial_lse, context_lens, batch, num_q_heads, head_dim,
+        partition_size, prefix_len, prefix_partition_size, group_len, max_partitions, out,
+        stream))
 
 
 def paged_attn_reduce_cascade(partial_out, partial_lse, context_lens, batch, num_q_heads,
                               head_dim, partition_size, prefix_len, prefix_partition_size,
                               max_partitions, out, stream=None) -> None:
-    _check(_lib.paged_attn_reduce_cascade(_ptr(partial_out), _ptr(partial_lse),
-                                          _ptr(context_lens), batch, num_q_heads, head_dim,
+    _check(_pycall.paged_attn_reduce_cascade(partial_out, partial_lse,
+                                          context_lens, batch, num_q_heads, head_dim,
                                           partition_size, prefix_len, prefix_partition_size,
-                                          max_partitions, _ptr(out), _ptr(stream)))
+                                          max_partitions, out, stream))
 
 
 def paged_attn_extend(pool: KVPool, q, q_start, total_q, block_tables, bt_stride, context_lens, batch,
                       num_q_heads, scale, max_context_len, max_chunk, out, stream=None) -> None:
-    _check(_lib.paged_attn_extend(pool._handle(), _ptr(q), _ptr(q_start), total_q, _ptr(block_tables),
-                                  bt_stride, _ptr(context_lens), batch, num_q_heads, scale,
-                                  max_context_len, max_chunk, _ptr(out), _ptr(stream)))
+    _check(_pycall.paged_attn_extend(pool._handle(), q, q_start, total_q, block_tables,
+                                  bt_stride, context_lens, batch, num_q_heads, scale,
+                                  max_context_len, max_chunk, out, stream))
 
 
 def paged_attn_schedule(context_lens, max_context_len, partition_size, prefix_len=0):
@@ -402,21 +415,21 @@ def paged_attn_schedule(context_lens, max_context_len, partition_size, prefix_le
 def paged_attn_decode_scheduled(pool: KVPool, q, block_tables, bt_stride, context_lens, batch,
                                 num_q_heads, scale, max_context_len, partition_size, items, num_items,
                                 out, partial_out=None, partial_lse=None, stream=None) -> None:
-    _check(_lib.paged_attn_decode_scheduled(pool._handle(), _ptr(q), _ptr(block_tables), bt_stride,
-                                            _ptr(context_lens), batch, num_q_heads, scale,
-                                            max_context_len, partition_size, _ptr(items), num_items,
-                                            _ptr(out), _ptr(partial_out), _ptr(partial_lse),
-                                            _ptr(stream)))
+    _check(_pycall.paged_attn_decode_scheduled(pool._handle(), q, block_tables, bt_stride,
+                                            context_lens, batch, num_q_heads, scale,
+                                            max_context_len, partition_size, items, num_items,
+                                            out, partial_out, partial_lse,
+                                            stream))
 
 
 def paged_attn_decode_cascade_scheduled(pool: KVPool, q, block_tables, bt_stride, context_lens, batch,
                                         num_q_heads, scale, max_context_len, partition_size,
                                         prefix_len, prefix_partition_size, items, num_items,
                                         partial_out, partial_lse, stream=None) -> None:
-    _check(_lib.paged_attn_decode_cascade_scheduled(
-        pool._handle(), _ptr(q), _ptr(block_tables), bt_stride, _ptr(context_lens), batch,
+    _check(_pycall.paged_attn_decode_cascade_scheduled(
+        pool._handle(), q, block_tables, bt_stride, context_lens, batch,
         num_q_heads, scale, max_context_len, partition_size, prefix_len, prefix_partition_size,
-        _ptr(items), num_items, _ptr(partial_out), _ptr(partial_lse), _ptr(stream)))
+        items, num_items, partial_out, partial_lse, stream))
 
 
 def paged_attn_decode_scheduled_trace(pool: KVPool, q, block_tables, bt_stride, context_lens, batch,
@@ -480,6 +493,6 @@ NOALLOC_SCRATCH_BYTES = 64 << 20
 def paged_attn_decode_noalloc(pool: KVPool, q, block_tables, bt_stride, context_lens, batch,
                               num_q_heads, scale, max_context_len, partition_size, out,
                               stream=None) -> None:
-    _check(_lib.paged_attn_decode_noalloc(pool._handle(), _ptr(q), _ptr(block_tables), bt_stride,
-                                          _ptr(context_lens), batch, num_q_heads, scale,
-                                          max_context_len, partition_size, _ptr(out), _ptr(stream)))
+    _check(_pycall.paged_attn_decode_noalloc(pool._handle(), q, block_tables, bt_stride,
+                                          context_lens, batch, num_q_heads, scale,
+                                          max_context_len, partition_size, out, stream))

@@ -1,7 +1,9 @@
 """Build the gfx950 HIP library ``libpaged_attn.so`` in-tree with hipcc.
 
 Every source is compiled for gfx950 only, with packed-fp32 instruction
-selection disabled, and linked into one shared library next to this file.
+selection disabled, and linked into one shared library next to this file;
+``_pycall``, the CPython extension through which the binding makes its
+per-step calls, is built beside it with the host compiler.
 """
 from __future__ import annotations
 
@@ -9,6 +11,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -17,6 +20,7 @@ BUILD_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libpaged_attn.so")
 SOURCES = ["api.cpp", "decode_mfma.hip", "cascade.hip", "reduce.hip", "append.hip", "extend.hip",
            "stream_copy.hip", "gather_tiles.hip", "noalloc.hip"]
+PYCALL_PATH = os.path.join(HERE, "_pycall" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 ARCH = "gfx950"
 
 COMMON_FLAGS = [
@@ -31,6 +35,21 @@ def hipcc() -> str:
     if not os.path.exists(path):
         raise RuntimeError("hipcc not found; ROCm is required to build the library")
     return path
+
+
+def host_compiler() -> str:
+    path = shutil.which("g++") or "/opt/rocm/llvm/bin/clang++"
+    if not os.path.exists(path):
+        raise RuntimeError("no host C++ compiler found")
+    return path
+
+
+def build_pycall(verbose: bool = False) -> None:
+    tmp = PYCALL_PATH + ".tmp"
+    _run([host_compiler(), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden",
+          "-I", sysconfig.get_paths()["include"], "-I", os.path.join(HERE, "..", "include"),
+          os.path.join(CSRC, "pycall.cpp"), "-o", tmp], verbose)
+    os.replace(tmp, PYCALL_PATH)
 
 
 def _run(cmd, verbose):
@@ -61,6 +80,7 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
     tmp = LIB_PATH + ".tmp"
     _run([cc, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs], verbose)
     os.replace(tmp, LIB_PATH)
+    build_pycall(verbose)
     return LIB_PATH
 
 
