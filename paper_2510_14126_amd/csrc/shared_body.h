@@ -29,7 +29,10 @@
 //
 // What bounds it: the dependent chain of a stage (loads, LDS, QK^T, softmax,
 // PV).  Splitting the partition's tokens over the wavefronts instead of its
-// rows makes the chain four times shorter.
+// rows makes the chain four times shorter: three sequences over a 768-token
+// prefix, one partition, 27.7 -> 12.4 us a step.  extend_body.h uses the same
+// routine for small chunks.  Both sides of the choice are measured at
+// split_span (cascade.hip) and at launch_t (extend.hip).
 #pragma once
 
 #include "kernels.h"
