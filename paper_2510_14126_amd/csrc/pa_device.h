@@ -46,13 +46,14 @@ __device__ __forceinline__ void store_partial2(float* dst, float a, float b) {
 }
 
 // Four floats at dst (16-byte aligned) in one store of the same scope, for
-// which there is no atomic type.  The wait state keeps the next instruction
-// from overwriting the data registers too early (gfx9: one after a vector
-// store of more than 64 bits).
+// which there is no atomic type.  The compiler's hazard recognizer does not
+// look into inline assembly, so the block carries its own wait states: after a
+// vector store of more than 64 bits the gfx940 family needs two before a
+// vector instruction overwrites the data registers (s_nop 1; older gfx9 one).
 typedef float store_f4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void store_partial4(float* dst, float a, float b, float c, float d) {
   const store_f4_t v = {a, b, c, d};
-  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(dst), "v"(v) : "memory");
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(dst), "v"(v) : "memory");
 }
 
 // Cache-policy operand of a buffer load: bit 1 is the non-temporal hint of
