@@ -8,21 +8,31 @@
 // which is exactly softmax attention over the whole context (zeros when
 // every w_p is 0).  NW wavefronts per (b, h).  Lane q loads lse_q (64
 // partitions per round); the partitions' o rows are dealt to the wavefronts
-// in groups of kGroup, and each wavefront's first group is loaded together
-// with the context length, so up to NW * kGroup partitions cost one memory
-// round trip.  Lane l owns output dims (D/64)*l .. and adds its wavefront's
-// partitions in order (weights broadcast from the lane that computed them),
-// then the wavefronts' sums are added in order through LDS, so the result is
-// deterministic and P_b = 1 reproduces o_0 bit for bit.
+// in groups of kGroup, each group loaded together.  Lane l owns output dims
+// (D/64)*l .. and adds its wavefront's partitions in order (weights broadcast
+// from the lane that computed them), then the wavefronts' sums are added in
+// order through LDS, so the result is deterministic and P_b = 1 reproduces o_0
+// bit for bit.
+//
+// What bounds it: the round trips to memory (context length, then partials)
+// while rows are few, the bytes of the partials that exist while they are many.
+// A buffer sized for a long max_context_len holds many slots that no partition
+// wrote, so o rows are loaded after the context length says which exist, except
+// where the call is so small that the rest costs nothing (PRE, launch_t).
+// (Loading every slot's row with the length, whatever the call: 128 sequences
+// of 500 tokens under a bound of 32768, 64 heads, whole step 193 us, now 153;
+// 256 of 64..8192 in 512-token partitions 320, now 308.)
 #include "kernels.h"
 #include "pa_device.h"
+
+#include <algorithm>
 
 namespace pa {
 namespace {
 
 constexpr int kGroup = 8;   // partitions whose o rows a wavefront loads together
 
-template <int D, int NW>
+template <int D, int NW, bool PRE>
 __global__ void __launch_bounds__(64 * NW) reduce_kernel(const ReduceParams p) {
   constexpr int DPL = D / 64;
   const int lane = threadIdx.x & 63;
@@ -33,7 +43,7 @@ __global__ void __launch_bounds__(64 * NW) reduce_kernel(const ReduceParams p) {
   const float* po = p.part_o + (size_t)bh * p.part_stride * D + DPL * lane;
 
   // o rows of partitions first .. first+kGroup-1 (clamped to `lastq`; what
-  // lies past P_b may hold anything and is never used)
+  // lies past P_b, also lse, may hold anything and is never used)
   float v[kGroup][DPL];
   auto load_group = [&](int first, int lastq) {
 #pragma unroll
@@ -44,12 +54,15 @@ __global__ void __launch_bounds__(64 * NW) reduce_kernel(const ReduceParams p) {
     }
   };
   const float x0 = lane < p.part_stride ? lse[lane] : 0.f;
-  load_group(wave * kGroup, p.part_stride - 1);
+  if constexpr (PRE) load_group(wave * kGroup, p.part_stride - 1);
 
   int n = p.context_lens[b] - p.prefix_len;
   n = n < 0 ? 0 : n;
   int pb = p.prefix_parts + n / p.part_tokens + (n % p.part_tokens != 0);
   pb = pb > p.part_stride ? p.part_stride : pb;
+  if constexpr (!PRE) {
+    if (wave * kGroup < pb) load_group(wave * kGroup, pb - 1);
+  }
   const float l0 = lane < pb ? x0 : -__builtin_inff();
 
   float mx = l0;
@@ -87,9 +100,11 @@ __global__ void __launch_bounds__(64 * NW) reduce_kernel(const ReduceParams p) {
     if (wave != 0) return;
 #pragma unroll
     for (int w = 1; w < NW; ++w) {
-      wsum += sw[w];
+      if (w * kGroup < pb) {
+        wsum += sw[w];
 #pragma unroll
-      for (int d = 0; d < DPL; ++d) o[d] += so[w][DPL * lane + d];
+        for (int d = 0; d < DPL; ++d) o[d] += so[w][DPL * lane + d];
+      }
     }
   }
   const float inv = wsum > 0.f ? 1.0f / wsum : 0.f;
@@ -100,18 +115,42 @@ __global__ void __launch_bounds__(64 * NW) reduce_kernel(const ReduceParams p) {
     orow[lane] = (uint16_t)bf16_rne(o[0] * inv);
 }
 
+// The eight-wavefront form is for calls of few rows: up to kWideRows of them
+// their wavefronts fit the GPU at once.  Whole step, one / eight wavefronts: one
+// sequence of 59 partitions, 64 rows, 26.6 / 24.2 us, 256 rows of 59 88.7 / 86.6,
+// 512 171.6 / 169.9; 1024 333.4 / 333.2, 2048 666 / 667, and with short contexts
+// under a bound of 64 partitions 1024 rows 27.1 / 27.9, 8192 153 / 162.
+constexpr int64_t kWideRows = 512;
+// Most bytes of o rows that a call may load in vain before the context lengths
+// arrive.  Up to 4 MB they cost less than the round trip they save; whole step,
+// with / without the early loads: 64 rows of 59 partitions 23.6 / 24.2 us, 128 rows
+// 45.0 / 45.5, 2048 of five 30.9 / 31.1; 64 and 128 rows of one partition under a
+// bound of 64 (2 and 4 MB) the same, 256 (8 MB) 12.9 / 12.4, 2048 of one under a
+// bound of six (5 MB) 18.4 / 17.9, of eight (7 MB) 20.2 / 18.8.
+constexpr int64_t kPreloadBytes = (int64_t)4 << 20;
+
+template <int D, int NW>
+void launch_nw(const ReduceParams& p, bool pre, hipStream_t stream) {
+  const dim3 grd((unsigned)((int64_t)p.batch * p.num_q_heads));
+  if (pre)
+    hipLaunchKernelGGL((reduce_kernel<D, NW, true>), grd, dim3(64 * NW), 0, stream, p);
+  else
+    hipLaunchKernelGGL((reduce_kernel<D, NW, false>), grd, dim3(64 * NW), 0, stream, p);
+}
+
 template <int D>
 void launch_t(const ReduceParams& p, hipStream_t stream) {
-  const dim3 grd((unsigned)((int64_t)p.batch * p.num_q_heads));
-  // One wavefront per row while its single group holds every partition; eight
-  // beyond (1 / 2 / 4 / 8 wavefronts: one sequence of 59 partitions, 64 heads,
-  // whole step 28.2 / 26.6 / 25.9 / 25.4 us; 8192 rows of 16..64 partitions,
-  // whole step 1501 / 1502 / 1501 / 1482 us).
   constexpr int kWide = 8;
-  if (p.part_stride <= kGroup)
-    hipLaunchKernelGGL((reduce_kernel<D, 1>), grd, dim3(64), 0, stream, p);
+  const int64_t rows = (int64_t)p.batch * p.num_q_heads;
+  const bool wide = p.part_stride > kGroup && rows <= kWideRows;
+  // slots loaded early, less those that every sequence (of at least one token) has
+  const int early = std::min(p.part_stride, kGroup * (wide ? kWide : 1));
+  const int vain = std::max(early - std::max(p.prefix_parts, 1), 0);
+  const bool pre = rows * vain * D * (int64_t)sizeof(float) <= kPreloadBytes;
+  if (wide)
+    launch_nw<D, kWide>(p, pre, stream);
   else
-    hipLaunchKernelGGL((reduce_kernel<D, kWide>), grd, dim3(64 * kWide), 0, stream, p);
+    launch_nw<D, 1>(p, pre, stream);
 }
 
 }  // namespace
