@@ -21,8 +21,6 @@ struct pa_kv_pool {
   std::vector<int32_t> refcount;  // 0 = free
   std::vector<int32_t> free_stack; // top = back(); ids pop in ascending order initially
   int64_t shared_blocks = 0;       // blocks whose reference count is 2 or more
-  int64_t refs = 0;                // references of all blocks
-  int64_t shared_refs = 0;         // references of the blocks with two or more
 };
 
 namespace {
@@ -139,21 +137,6 @@ int validate_decode(const DecodeArgs& a, int32_t* group, const char* fn) {
 // partitions, while partition-major is faster for a few partitions).
 int32_t item_order_for(int32_t num_parts) { return num_parts >= 16 ? 1 : 0; }
 
-// Whether the plain decode loads its tiles with the streaming cache hint.
-// With no block shared by two tables every tile is read once per step.  With
-// shared blocks the hint may cost their re-reads, but while at most a third of
-// all references are to shared blocks the rest gains more (one MI355X, 128
-// sequences of 64..8192 tokens, default / streaming: 2% of the references
-// shared 387 / 351 us, 11% 388 / 357, 20% 403 / 381, 33% 429 / 401) -- except
-// where the blocks in use may stay in the 256 MB Infinity Cache from one call
-// to the next (16 sequences of up to 1100 tokens, 35 MB: 11.0 / 12.7 us).
-bool stream_tiles(const pa_kv_pool* pool) {
-  if (pool->shared_refs == 0) return true;
-  const int64_t used = pool->num_blocks - (int64_t)pool->free_stack.size();
-  const int64_t bytes = used * pool->num_kv_heads * PA_BLOCK_SIZE * pool->head_dim * 2 * 2;
-  return 3 * pool->shared_refs <= pool->refs && bytes >= (int64_t)256 << 20;
-}
-
 pa::DecodeParams decode_params(const DecodeArgs& a) {
   pa::DecodeParams p{};
   p.k_pool = a.pool->k;
@@ -168,7 +151,9 @@ pa::DecodeParams decode_params(const DecodeArgs& a) {
   p.batch = a.batch;
   p.bt_stride = a.bt_stride;
   p.max_ctx = a.max_context_len;
-  p.stream_tiles = stream_tiles(a.pool) ? 1 : 0;
+  // With no block shared by two tables every tile is read once per step:
+  // stream it past the caches.
+  p.stream_tiles = a.pool->shared_blocks == 0 ? 1 : 0;
   p.scale_log2 = a.scale * 1.4426950408889634f;
   if (a.k_new) {
     p.k_new = static_cast<const uint16_t*>(a.k_new);
@@ -361,7 +346,6 @@ int kv_pool_alloc(pa_kv_pool* pool, int32_t n, int32_t* ids_out) {
     pool->refcount[id] = 1;
     ids_out[i] = id;
   }
-  pool->refs += n;
   return PA_OK;
 }
 
@@ -376,7 +360,6 @@ int kv_pool_claim(pa_kv_pool* pool, int32_t n, const int32_t* ids) {
     seen[ids[i]] = 1;
   }
   for (int32_t i = 0; i < n; ++i) pool->refcount[ids[i]] = 1;
-  pool->refs += n;
   rebuild_free(pool);
   return PA_OK;
 }
@@ -391,12 +374,8 @@ int kv_pool_retain(pa_kv_pool* pool, int32_t n, const int32_t* ids) {
     if (pool->refcount[ids[i]] == 0x7fffffff)
       return fail(PA_ESTATE, "kv_pool_retain: reference count of block %d overflows", ids[i]);
   }
-  for (int32_t i = 0; i < n; ++i) {
-    const bool second = ++pool->refcount[ids[i]] == 2;
-    if (second) ++pool->shared_blocks;
-    pool->shared_refs += second ? 2 : 1;
-  }
-  pool->refs += n;
+  for (int32_t i = 0; i < n; ++i)
+    if (++pool->refcount[ids[i]] == 2) ++pool->shared_blocks;
   return PA_OK;
 }
 
@@ -412,9 +391,7 @@ int kv_pool_release(pa_kv_pool* pool, int32_t n, const int32_t* ids) {
     const int32_t left = --pool->refcount[ids[i]];
     if (left == 0) freed = true;
     if (left == 1) --pool->shared_blocks;
-    if (left > 0) pool->shared_refs -= left == 1 ? 2 : 1;
   }
-  pool->refs -= n;
   if (freed) rebuild_free(pool);
   return PA_OK;
 }
