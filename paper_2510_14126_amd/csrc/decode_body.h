@@ -40,8 +40,8 @@
 // Measured against the kernels this one took the place of (VALU dot products
 // for G = 4 and for D = 64, two MFMAs per PV step for G = 8 at D = 128; whole
 // step, one MI355X): 64 sequences over a shared 2048-token prefix without the
-// cascade 70 -> 42.6 us, 48 sequences of 61..4093 tokens at D = 64 45 -> 30
-// us, 4 of 100..300 tokens 6.7 -> 5.1 us, 256 of 64..8192 tokens 239 -> 237
+// cascade 70 -> 42.6 us, 48 sequences of 61..4093 tokens at D = 64 40.7 -> 28.2
+// us, 4 of 100..300 tokens 6.8 -> 4.8 us, 256 of 64..8192 tokens 239 -> 237
 // us (6.6 TB/s, what the same tiles take without arithmetic).  The VALU form
 // issued about 250 instructions per block, this one about 100.
 //

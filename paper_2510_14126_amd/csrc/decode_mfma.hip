@@ -14,14 +14,17 @@ using mfma::kWaves;
 // wavefronts.  Where sequences share blocks the tiles come from L2, the items
 // are short of latency hiding, not of bandwidth, and two tiles (154 VGPRs:
 // three wavefronts per SIMD) win: 64 sequences over a shared 2048-token
-// prefix 47.7 -> 42.6 us.  At D = 64 a tile is half the bytes: four tiles at
-// three wavefronts (130 VGPRs) against five at two: 4 sequences of 100..300
-// tokens 5.3 -> 5.0 us, 48 of 61..4093 tokens 30.6 -> 30.0 us.
+// prefix 47.7 -> 42.6 us.  At D = 64 a tile is half the bytes, and the loads
+// past an item's end, NBUF - 1 per wavefront, weigh more than the depth gains:
+// four / three / two tiles, whole step, 48 sequences of 61..4093 tokens 29.0 /
+// 28.6 / 28.2 us, 256 of 256 27.8 / 25.3 / 23.2, 64 over a shared 2048-token
+// prefix 24.6 / 23.3 / 21.5, 256 of 64..8192 in 512-token partitions 413 / 397 /
+// 383 (VALU kernel 407), in one partition 391 / 394 / 386.
 template <int D, bool STREAM>
-constexpr int nbuf() { return D == 64 ? 4 : (STREAM ? 3 : 2); }
+constexpr int nbuf() { return D == 128 && STREAM ? 3 : 2; }
 
 template <int D, int G, bool TRACE, bool STREAM, bool APPEND>
-__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2, 8)))
+__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 8)))
 decode_mfma_kernel(const DecodeParams p) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[decode::lds_bytes<D, G, STREAM>()];
   decode::decode_body<D, G, nbuf<D, STREAM>(), TRACE, STREAM, APPEND>(p, blockIdx.x, (lds_u8_t*)smem);
