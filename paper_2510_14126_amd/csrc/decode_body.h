@@ -255,7 +255,7 @@ constexpr int lds_bytes() {
 // 2048-token prefix, 512-token partitions, no cascade: 42.7 -> 33.6 us a step;
 // with the even sequence always computing, no change: half of the shader
 // engines had all the work.)
-template <int D, int G, int NBUF, bool TRACE, bool STREAM, bool APPEND>
+template <int D, int G, int NBUF, bool TRACE, bool STREAM, bool APPEND, bool ONE_MERGE = false>
 __device__ __forceinline__ void decode_body(const DecodeParams& p, int wg_index, lds_u8_t* smem) {
   constexpr int VW = D / 32;
   constexpr int DPL = D / 16;   // dims per lane and token row
@@ -493,10 +493,13 @@ __device__ __forceinline__ void decode_body(const DecodeParams& p, int wg_index,
   // cost the 8K-32K-token step 0.6%).  All wavefronts merge, a few rows each:
   // against one wavefront merging every row, one long sequence's step takes
   // 25.1 instead of 26.4 us and a one-KV-head batch's 55.4 instead of 57.1 us.
+  // ONE_MERGE has wavefront 0 do it (decode_mfma.hip, one_merge).
+  constexpr int kMergeWaves = ONE_MERGE ? 1 : kWaves;
   constexpr int kRowThreads = D / 2;
-  constexpr int kRowsPerPass = 64 * kWaves / kRowThreads;
+  constexpr int kRowsPerPass = 64 * kMergeWaves / kRowThreads;
   const int d = 2 * (threadIdx.x % kRowThreads);
   const int rows = PAIR && paired ? 2 * G : G;
+  if (wave >= kMergeWaves) return;
 #pragma unroll
   for (int r0 = 0; r0 < kMergeRows; r0 += kRowsPerPass) {
     const int r = r0 + threadIdx.x / kRowThreads;

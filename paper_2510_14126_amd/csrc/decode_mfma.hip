@@ -23,11 +23,27 @@ using mfma::kWaves;
 template <int D, bool STREAM>
 constexpr int nbuf() { return D == 128 && STREAM ? 3 : 2; }
 
-template <int D, int G, bool TRACE, bool STREAM, bool APPEND>
-__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 8)))
+template <int D, int G, bool TRACE, bool STREAM, bool APPEND, bool ONE_MERGE>
+__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, ONE_MERGE && G == 8 ? 2 : 8)))
 decode_mfma_kernel(const DecodeParams p) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[decode::lds_bytes<D, G, STREAM>()];
-  decode::decode_body<D, G, nbuf<D, STREAM>(), TRACE, STREAM, APPEND>(p, blockIdx.x, (lds_u8_t*)smem);
+  decode::decode_body<D, G, nbuf<D, STREAM>(), TRACE, STREAM, APPEND, ONE_MERGE>(p, blockIdx.x, (lds_u8_t*)smem);
+}
+
+// Whether one wavefront merges and stores an item's rows, and at G = 8 two
+// wavefronts per SIMD run instead of three: for long contexts with the default
+// cache policy (D = 128), where the stores of many items that end at once, all
+// four wavefronts of each, hold up the loads of the others.  Whole step, four /
+// one storing wavefronts (G = 8: three / two per SIMD), G = 8: 128 sequences of
+// 8K-32K tokens over 4096 shared ones 1698 / 1677 us, 64 of 8K-32K 1029 / 1018, in
+// 1024-token partitions 992 / 975, 64 of 4K-16K (16384 workgroups) 508 / 498; G = 4:
+// 1582 / 1561, 974 / 969, 949 / 948, 479 / 476.  The other side: 128 of up to 8K in
+// 16 partitions, G = 8, 464 / 474, in 32 of 256 tokens 492 / 496, 8 of 8K-32K (4096
+// workgroups) 131.4 / 132.4, short contexts over shared blocks 42 / 46; streaming
+// 910 / 916.
+bool one_merge(const DecodeParams& p) {
+  return p.head_dim == 128 && p.part_tokens >= 512 && p.num_parts >= 32 &&
+         (int64_t)p.num_parts * p.batch * p.num_kv_heads >= 16384;
 }
 
 // The trace kernel keeps the default cache policy (the hint changes no
@@ -36,18 +52,24 @@ template <int D, int G>
 hipError_t launch_t(const DecodeParams& p, bool trace, hipStream_t stream) {
   const int64_t grid = decode_items(p) * p.num_kv_heads;
   if (grid == 0) return hipSuccess;
-  const dim3 grd((unsigned)grid), blk(64 * kWaves);
   const bool append = p.k_new != nullptr;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * kWaves), 0, stream, p);
+  };
   if (trace)
-    hipLaunchKernelGGL((decode_mfma_kernel<D, G, true, false, false>), grd, blk, 0, stream, p);
+    go(decode_mfma_kernel<D, G, true, false, false, false>);
   else if (p.stream_tiles && append)
-    hipLaunchKernelGGL((decode_mfma_kernel<D, G, false, true, true>), grd, blk, 0, stream, p);
+    go(decode_mfma_kernel<D, G, false, true, true, false>);
   else if (p.stream_tiles)
-    hipLaunchKernelGGL((decode_mfma_kernel<D, G, false, true, false>), grd, blk, 0, stream, p);
+    go(decode_mfma_kernel<D, G, false, true, false, false>);
+  else if (one_merge(p) && append)
+    go(decode_mfma_kernel<D, G, false, false, true, D == 128>);
+  else if (one_merge(p))
+    go(decode_mfma_kernel<D, G, false, false, false, D == 128>);
   else if (append)
-    hipLaunchKernelGGL((decode_mfma_kernel<D, G, false, false, true>), grd, blk, 0, stream, p);
+    go(decode_mfma_kernel<D, G, false, false, true, false>);
   else
-    hipLaunchKernelGGL((decode_mfma_kernel<D, G, false, false, false>), grd, blk, 0, stream, p);
+    go(decode_mfma_kernel<D, G, false, false, false, false>);
   return hipGetLastError();
 }
 

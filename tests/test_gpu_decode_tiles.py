@@ -180,6 +180,50 @@ def run_step(w, S, schedule=False, new=None):
     return out
 
 
+@pytest.mark.parametrize("append", [False, True])
+@pytest.mark.parametrize("group", [4, 8])
+def test_long_contexts_over_shared_blocks(group, append):
+    """Both sides of the line from which one wavefront merges an item's rows
+    (32 partitions of 512 tokens and 16384 workgroups in the grid: 64 sequences
+    under a max_context_len of 16384, or 63): the same bits for the sequences
+    that both batches hold, and what the oracle gives."""
+    from types import SimpleNamespace
+    from paper_2510_14126_amd.device import PagedBatch
+    print(f"[gpu case] long contexts over shared blocks, group {group}, append {append}", flush=True)
+    lens = [16384, 16383, 513, 3100, 0, 512, 1] + list(range(40, 40 + 57))
+    if append:
+        lens[4] = 17
+    shared = 0 if append else 32                 # an appended block belongs to its sequence
+    w, k, v = wide_batch(8, group, 1024, shared, lens)
+    new = [torch.randn((64, 8, 128), dtype=torch.bfloat16, device="cuda:0") for _ in range(2)]
+    outs = []
+    for batch in (64, 63):
+        x = SimpleNamespace(**{**vars(w), "batch": batch, "context_lens": w.context_lens[:batch],
+                               "block_tables": w.block_tables[:batch], "q": w.q[:batch]})
+        pb = PagedBatch(x, "cuda:0", k_pool=k.clone(), v_pool=v.clone(), register_blocks=False)
+        one_shared_block(pb)
+        pb.out.fill_(0x7FC0)
+        pb.decode_append(*(t[:batch].contiguous() for t in new)) if append else pb.decode()
+        pb.reduce()
+        torch.cuda.synchronize()
+        outs.append(pb.out_bits()[:63])
+        w.k_pool, w.v_pool = (t.view(torch.int16).cpu().numpy().view(np.uint16) for t in (pb.k, pb.v))
+        pb.close()
+    assert np.array_equal(outs[0], outs[1])
+    w.batch = 63
+    for name in ("q", "context_lens", "block_tables"):
+        setattr(w, name, getattr(w, name)[:63])
+    rep = compare(outs[0], decode_workload(w)[0])
+    assert rep.passed, f"{rep}"
+
+
+def one_shared_block(pb):
+    """A pool that knows one shared block: the default cache policy."""
+    from paper_2510_14126_amd import binding
+    ids = binding.kv_pool_alloc(pb.pool, 1)
+    binding.kv_pool_retain(pb.pool, ids)
+
+
 @pytest.mark.parametrize("group", [4, 8])
 def test_head64_items_keep_up_with_their_gather(group):
     """256 sequences of 256 tokens at D = 64 against the same tiles read with no
