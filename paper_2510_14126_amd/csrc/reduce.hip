@@ -18,7 +18,8 @@
 // while rows are few, the bytes of the partials that exist while they are many.
 // A buffer sized for a long max_context_len holds many slots that no partition
 // wrote, so o rows are loaded after the context length says which exist, except
-// where the call is so small that the rest costs nothing (PRE, launch_t).
+// where the call is so small that the rest costs nothing (PRE, launch_t).  Large
+// buffers are read with the streaming hint (STREAM, kStreamBytes).
 // (Loading every slot's row with the length, whatever the call: 128 sequences
 // of 500 tokens under a bound of 32768, 64 heads, whole step 193 us, now 153;
 // 256 of 64..8192 in 512-token partitions 320, now 308.)
@@ -32,7 +33,7 @@ namespace {
 
 constexpr int kGroup = 8;   // partitions whose o rows a wavefront loads together
 
-template <int D, int NW, bool PRE>
+template <int D, int NW, bool PRE, bool STREAM>
 __global__ void __launch_bounds__(64 * NW) reduce_kernel(const ReduceParams p) {
   constexpr int DPL = D / 64;
   const int lane = threadIdx.x & 63;
@@ -50,7 +51,10 @@ __global__ void __launch_bounds__(64 * NW) reduce_kernel(const ReduceParams p) {
     for (int k = 0; k < kGroup; ++k) {
       const int q = min(first + k, lastq);
 #pragma unroll
-      for (int d = 0; d < DPL; ++d) v[k][d] = po[(size_t)q * D + d];
+      for (int d = 0; d < DPL; ++d) {
+        const float* x = po + (size_t)q * D + d;
+        v[k][d] = STREAM ? __builtin_nontemporal_load(x) : *x;
+      }
     }
   };
   const float x0 = lane < p.part_stride ? lse[lane] : 0.f;
@@ -100,11 +104,9 @@ __global__ void __launch_bounds__(64 * NW) reduce_kernel(const ReduceParams p) {
     if (wave != 0) return;
 #pragma unroll
     for (int w = 1; w < NW; ++w) {
-      if (w * kGroup < pb) {
-        wsum += sw[w];
+      wsum += sw[w];
 #pragma unroll
-        for (int d = 0; d < DPL; ++d) o[d] += so[w][DPL * lane + d];
-      }
+      for (int d = 0; d < DPL; ++d) o[d] += so[w][DPL * lane + d];
     }
   }
   const float inv = wsum > 0.f ? 1.0f / wsum : 0.f;
@@ -129,13 +131,29 @@ constexpr int64_t kWideRows = 512;
 // bound of six (5 MB) 18.4 / 17.9, of eight (7 MB) 20.2 / 18.8.
 constexpr int64_t kPreloadBytes = (int64_t)4 << 20;
 
+// Size of the partial buffer from which its rows are loaded with the streaming
+// hint: more than the eight 4 MB L2s hold.  The decode left those rows dirty in the
+// caches and nobody reads them again; with default loads they stay, and their
+// write-back takes bandwidth from the next decode.  128 sequences of 8K-32K tokens
+// (268 MB), whole step, default / streaming, one batch again and again 1441 / 1417
+// us, two batches in turn 1500 / 1433; 256 of 64..8192 in 512-token partitions (67
+// MB) 308.6 / 307.4.  In 5 MB it costs: 64 over a shared 2048-token prefix, three
+// batches in turn, 23.8 / 24.1.
+constexpr int64_t kStreamBytes = (int64_t)32 << 20;
+
 template <int D, int NW>
 void launch_nw(const ReduceParams& p, bool pre, hipStream_t stream) {
-  const dim3 grd((unsigned)((int64_t)p.batch * p.num_q_heads));
-  if (pre)
-    hipLaunchKernelGGL((reduce_kernel<D, NW, true>), grd, dim3(64 * NW), 0, stream, p);
+  const int64_t rows = (int64_t)p.batch * p.num_q_heads;
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)rows), dim3(64 * NW), 0, stream, p); };
+  const bool nt = rows * p.part_stride * D * (int64_t)sizeof(float) > kStreamBytes;
+  if (pre && nt)
+    go(reduce_kernel<D, NW, true, true>);
+  else if (pre)
+    go(reduce_kernel<D, NW, true, false>);
+  else if (nt)
+    go(reduce_kernel<D, NW, false, true>);
   else
-    hipLaunchKernelGGL((reduce_kernel<D, NW, false>), grd, dim3(64 * NW), 0, stream, p);
+    go(reduce_kernel<D, NW, false, false>);
 }
 
 template <int D>

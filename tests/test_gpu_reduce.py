@@ -74,29 +74,36 @@ def test_slots_that_no_partition_wrote_are_not_read():
     assert loose <= tight + 10.0, (loose, tight)
 
 
+@pytest.mark.parametrize("prefix", [0, 8])
 @pytest.mark.parametrize("rows_b", [4, 8, 9, 40])
-@pytest.mark.parametrize("stride", [8, 9, 65])
-def test_reduce_forms(rows_b, stride):
+@pytest.mark.parametrize("stride", [8, 9, 65, 130])
+def test_reduce_forms(rows_b, stride, prefix):
     """Both sides of the lines between the kernel's forms (64 heads: 512 | 576
-    rows; early loads up to 4 MB) give the float64 merge, with NaN in every slot
-    that no partition wrote and sequences of none, some and all partitions."""
+    rows; early loads of up to 4 MB that may be in vain; streaming loads beyond
+    32 MB of partials) give the float64 merge, with NaN in every slot that no
+    partition wrote and sequences of none, some and all partitions after those
+    that all have."""
     from paper_2510_14126_amd import binding
-    print(f"[gpu case] reduce forms rows={64 * rows_b} partitions={stride}", flush=True)
+    print(f"[gpu case] reduce forms rows={64 * rows_b} partitions={stride} prefix={prefix}", flush=True)
     S, hq, d = 16, 64, 128
-    parts = np.array([(0, 1, stride, stride // 2)[i % 4] for i in range(rows_b)])
+    parts = np.array([max(prefix, (0, 1, stride, stride // 2)[i % 4]) for i in range(rows_b)])
     rng = np.random.default_rng(520 + stride)
     o = np.full((rows_b, hq, stride, d), np.nan, np.float32)
     lse = np.full((rows_b, hq, stride), np.nan, np.float32)
     ref = np.zeros((rows_b, hq, d))
     for b, p in enumerate(parts):
         if p:
-            o[b, :, :p] = rng.standard_normal((hq, p, d))
+            o[b, :, :p] = rng.standard_normal((hq, p, d), dtype=np.float32)
             lse[b, :, :p] = 3 * rng.standard_normal((hq, p))
             w = np.exp(lse[b, :, :p].astype(np.float64) - lse[b, :, :p].max(axis=1, keepdims=True))
-            ref[b] = (w[:, :, None] * o[b, :, :p]).sum(axis=1) / w.sum(axis=1)[:, None]
+            ref[b] = (w[:, None, :] @ o[b, :, :p].astype(np.float64))[:, 0] / w.sum(axis=1)[:, None]
     out = torch.full((rows_b, hq, d), 0x7FC0, dtype=torch.int16, device="cuda:0")
-    binding.paged_attn_reduce(torch.from_numpy(o).cuda(), torch.from_numpy(lse).cuda(),
-                              torch.from_numpy((parts * S).astype(np.int32)).cuda(), rows_b, hq, d, S, stride, out)
+    args = [torch.from_numpy(o).cuda(), torch.from_numpy(lse).cuda(),
+            torch.from_numpy((parts * S).astype(np.int32)).cuda(), rows_b, hq, d, S]
+    if prefix:
+        binding.paged_attn_reduce_cascade(*args, prefix * S, S, stride, out)
+    else:
+        binding.paged_attn_reduce(*args, stride, out)
     torch.cuda.synchronize()
     got = bf16_to_f64(out.cpu().numpy().view(np.uint16))
     assert np.all(np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-5 * np.abs(ref).max(axis=2, keepdims=True))
