@@ -8,12 +8,14 @@ passed) or as raw integer addresses; ``stream`` is a HIP stream handle as an
 integer (for example ``torch.cuda.current_stream().cuda_stream``) or None
 for the default stream.  A negative status raises ``PagedAttnError`` with
 the library's message.  If the library has not been built, importing this
-module raises ImportError: there is no fallback path.
+module raises ImportError: there is no fallback path.  (Without the extension
+the same calls go through ctypes, about 2 us of host time slower each.)
 """
 from __future__ import annotations
 
 import ctypes
 import os
+from types import SimpleNamespace
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libpaged_attn.so")
@@ -115,19 +117,41 @@ def _load(path: str = LIB_PATH) -> ctypes.CDLL:
     return lib
 
 
-def _load_pycall(lib: ctypes.CDLL):
-    """The native calls of the per-step functions, bound to ``lib``."""
+# The functions a serving loop calls every step: called natively where the
+# _pycall extension can be loaded.
+PER_STEP = ("paged_attn_decode", "paged_attn_decode_scheduled", "paged_attn_reduce", "paged_attn_decode_cascade",
+            "paged_attn_decode_cascade_scheduled", "paged_attn_decode_cascade_groups", "paged_attn_reduce_cascade",
+            "paged_attn_reduce_cascade_groups", "paged_attn_append_kv", "paged_attn_decode_append",
+            "paged_attn_decode_cascade_append", "paged_attn_decode_noalloc", "paged_attn_extend")
+
+
+def _ctypes_call(lib: ctypes.CDLL, name: str):
+    """``lib``'s function, its pointers given as None, integers or tensors."""
+    fn = getattr(lib, name)
+    pointer = [t is _vp for t in fn.argtypes]
+
+    def call(*args):
+        return fn(*[_ptr(a) if p else a for a, p in zip(args, pointer)])
+    return call
+
+
+def _load_calls(lib: ctypes.CDLL):
+    """The calls of the per-step functions.  The native ones convert their
+    arguments faster and hand those they cannot convert to the ctypes ones, so
+    both accept, return and raise the same; where the extension was not built,
+    or for another interpreter, the ctypes calls alone serve."""
+    plain = {name: _ctypes_call(lib, name) for name in PER_STEP}
     try:
         from . import _pycall
-    except ImportError as e:
-        raise ImportError("the _pycall extension is missing: build the library first "
-                          "(python -c 'import __graft_entry__ as g; g.build()')") from e
-    _pycall.bind({n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in _pycall.NAMES})
+    except ImportError:
+        return SimpleNamespace(**plain)
+    _pycall.bind({name: (ctypes.cast(getattr(lib, name), ctypes.c_void_p).value, call)
+                  for name, call in plain.items()})
     return _pycall
 
 
 _lib = _load()
-_pycall = _load_pycall(_lib)
+_pycall = _load_calls(_lib)
 
 
 def library() -> ctypes.CDLL:
@@ -268,17 +292,15 @@ def paged_attn_workspace_size(batch, num_q_heads, head_dim, max_context_len, par
 def paged_attn_decode(pool: KVPool, q, block_tables, bt_stride, context_lens, batch, num_q_heads,
                       scale, max_context_len, partition_size, out, partial_out=None,
                       partial_lse=None, stream=None) -> None:
-    _check(_pycall.paged_attn_decode(pool._handle(), q, block_tables, bt_stride,
-                                  context_lens, batch, num_q_heads, scale, max_context_len,
-                                  partition_size, out, partial_out, partial_lse,
-                                  stream))
+    _check(_pycall.paged_attn_decode(pool._handle(), q, block_tables, bt_stride, context_lens,
+                                     batch, num_q_heads, scale, max_context_len, partition_size,
+                                     out, partial_out, partial_lse, stream))
 
 
 def paged_attn_reduce(partial_out, partial_lse, context_lens, batch, num_q_heads, head_dim,
                       partition_size, max_partitions, out, stream=None) -> None:
-    _check(_pycall.paged_attn_reduce(partial_out, partial_lse, context_lens, batch,
-                                  num_q_heads, head_dim, partition_size, max_partitions, out,
-                                  stream))
+    _check(_pycall.paged_attn_reduce(partial_out, partial_lse, context_lens, batch, num_q_heads,
+                                     head_dim, partition_size, max_partitions, out, stream))
 
 
 def paged_attn_decode_trace(pool: KVPool, q, block_tables, bt_stride, context_lens, batch,
@@ -304,17 +326,17 @@ def pa_gather_tiles(pool: KVPool, block_tables, bt_stride, batch, spans, num_spa
 
 def paged_attn_append_kv(pool: KVPool, k_new, v_new, block_tables, bt_stride, context_lens, batch,
                          stream=None) -> None:
-    _check(_pycall.paged_attn_append_kv(pool._handle(), k_new, v_new, block_tables,
-                                     bt_stride, context_lens, batch, stream))
+    _check(_pycall.paged_attn_append_kv(pool._handle(), k_new, v_new, block_tables, bt_stride,
+                                        context_lens, batch, stream))
 
 
 def paged_attn_decode_append(pool: KVPool, q, k_new, v_new, block_tables, bt_stride, context_lens,
                              batch, num_q_heads, scale, max_context_len, partition_size, items,
                              num_items, out, partial_out=None, partial_lse=None, stream=None) -> None:
-    _check(_pycall.paged_attn_decode_append(
-        pool._handle(), q, k_new, v_new, block_tables, bt_stride,
-        context_lens, batch, num_q_heads, scale, max_context_len, partition_size, items,
-        num_items, out, partial_out, partial_lse, stream))
+    _check(_pycall.paged_attn_decode_append(pool._handle(), q, k_new, v_new, block_tables,
+                                            bt_stride, context_lens, batch, num_q_heads, scale,
+                                            max_context_len, partition_size, items, num_items, out,
+                                            partial_out, partial_lse, stream))
 
 
 def paged_attn_decode_cascade_append(pool: KVPool, q, k_new, v_new, block_tables, bt_stride,
@@ -323,10 +345,9 @@ def paged_attn_decode_cascade_append(pool: KVPool, q, k_new, v_new, block_tables
                                      num_groups, max_group_size, group_len, items, num_items,
                                      partial_out, partial_lse, stream=None) -> None:
     _check(_pycall.paged_attn_decode_cascade_append(
-        pool._handle(), q, k_new, v_new, block_tables, bt_stride,
-        context_lens, batch, num_q_heads, scale, max_context_len, partition_size, prefix_len,
-        prefix_partition_size, group_start, num_groups, max_group_size, group_len, items,
-        num_items, partial_out, partial_lse, stream))
+        pool._handle(), q, k_new, v_new, block_tables, bt_stride, context_lens, batch, num_q_heads,
+        scale, max_context_len, partition_size, prefix_len, prefix_partition_size, group_start,
+        num_groups, max_group_size, group_len, items, num_items, partial_out, partial_lse, stream))
 
 
 def paged_attn_cascade_workspace_size(batch, num_q_heads, head_dim, max_context_len,
@@ -344,10 +365,10 @@ def paged_attn_decode_cascade(pool: KVPool, q, block_tables, bt_stride, context_
                               num_q_heads, scale, max_context_len, partition_size, prefix_len,
                               prefix_partition_size, partial_out, partial_lse, stream=None) -> None:
     _check(_pycall.paged_attn_decode_cascade(pool._handle(), q, block_tables, bt_stride,
-                                          context_lens, batch, num_q_heads, scale,
-                                          max_context_len, partition_size, prefix_len,
-                                          prefix_partition_size, partial_out,
-                                          partial_lse, stream))
+                                             context_lens, batch, num_q_heads, scale,
+                                             max_context_len, partition_size, prefix_len,
+                                             prefix_partition_size, partial_out, partial_lse,
+                                             stream))
 
 
 def paged_attn_cascade_groups_workspace_size(batch, num_q_heads, head_dim, max_context_len,
@@ -367,35 +388,32 @@ def paged_attn_decode_cascade_groups(pool: KVPool, q, block_tables, bt_stride, c
                                      max_group_size, group_len, items, num_items, partial_out,
                                      partial_lse, stream=None) -> None:
     _check(_pycall.paged_attn_decode_cascade_groups(
-        pool._handle(), q, block_tables, bt_stride, context_lens, batch,
-        num_q_heads, scale, max_context_len, partition_size, prefix_len, prefix_partition_size,
-        group_start, num_groups, max_group_size, group_len, items, num_items,
-        partial_out, partial_lse, stream))
+        pool._handle(), q, block_tables, bt_stride, context_lens, batch, num_q_heads, scale,
+        max_context_len, partition_size, prefix_len, prefix_partition_size, group_start,
+        num_groups, max_group_size, group_len, items, num_items, partial_out, partial_lse, stream))
 
 
 def paged_attn_reduce_cascade_groups(partial_out, partial_lse, context_lens, batch, num_q_heads,
                                      head_dim, partition_size, prefix_len, prefix_partition_size,
                                      group_len, max_partitions, out, stream=None) -> None:
     _check(_pycall.paged_attn_reduce_cascade_groups(
-        partial_out, partial_lse, context_lens, batch, num_q_heads, head_dim,
-        partition_size, prefix_len, prefix_partition_size, group_len, max_partitions, out,
-        stream))
+        partial_out, partial_lse, context_lens, batch, num_q_heads, head_dim, partition_size,
+        prefix_len, prefix_partition_size, group_len, max_partitions, out, stream))
 
 
 def paged_attn_reduce_cascade(partial_out, partial_lse, context_lens, batch, num_q_heads,
                               head_dim, partition_size, prefix_len, prefix_partition_size,
                               max_partitions, out, stream=None) -> None:
-    _check(_pycall.paged_attn_reduce_cascade(partial_out, partial_lse,
-                                          context_lens, batch, num_q_heads, head_dim,
-                                          partition_size, prefix_len, prefix_partition_size,
-                                          max_partitions, out, stream))
+    _check(_pycall.paged_attn_reduce_cascade(partial_out, partial_lse, context_lens, batch,
+                                             num_q_heads, head_dim, partition_size, prefix_len,
+                                             prefix_partition_size, max_partitions, out, stream))
 
 
 def paged_attn_extend(pool: KVPool, q, q_start, total_q, block_tables, bt_stride, context_lens, batch,
                       num_q_heads, scale, max_context_len, max_chunk, out, stream=None) -> None:
-    _check(_pycall.paged_attn_extend(pool._handle(), q, q_start, total_q, block_tables,
-                                  bt_stride, context_lens, batch, num_q_heads, scale,
-                                  max_context_len, max_chunk, out, stream))
+    _check(_pycall.paged_attn_extend(pool._handle(), q, q_start, total_q, block_tables, bt_stride,
+                                     context_lens, batch, num_q_heads, scale, max_context_len,
+                                     max_chunk, out, stream))
 
 
 def paged_attn_schedule(context_lens, max_context_len, partition_size, prefix_len=0):
@@ -416,10 +434,9 @@ def paged_attn_decode_scheduled(pool: KVPool, q, block_tables, bt_stride, contex
                                 num_q_heads, scale, max_context_len, partition_size, items, num_items,
                                 out, partial_out=None, partial_lse=None, stream=None) -> None:
     _check(_pycall.paged_attn_decode_scheduled(pool._handle(), q, block_tables, bt_stride,
-                                            context_lens, batch, num_q_heads, scale,
-                                            max_context_len, partition_size, items, num_items,
-                                            out, partial_out, partial_lse,
-                                            stream))
+                                               context_lens, batch, num_q_heads, scale,
+                                               max_context_len, partition_size, items, num_items,
+                                               out, partial_out, partial_lse, stream))
 
 
 def paged_attn_decode_cascade_scheduled(pool: KVPool, q, block_tables, bt_stride, context_lens, batch,
@@ -427,9 +444,9 @@ def paged_attn_decode_cascade_scheduled(pool: KVPool, q, block_tables, bt_stride
                                         prefix_len, prefix_partition_size, items, num_items,
                                         partial_out, partial_lse, stream=None) -> None:
     _check(_pycall.paged_attn_decode_cascade_scheduled(
-        pool._handle(), q, block_tables, bt_stride, context_lens, batch,
-        num_q_heads, scale, max_context_len, partition_size, prefix_len, prefix_partition_size,
-        items, num_items, partial_out, partial_lse, stream))
+        pool._handle(), q, block_tables, bt_stride, context_lens, batch, num_q_heads, scale,
+        max_context_len, partition_size, prefix_len, prefix_partition_size, items, num_items,
+        partial_out, partial_lse, stream))
 
 
 def paged_attn_decode_scheduled_trace(pool: KVPool, q, block_tables, bt_stride, context_lens, batch,
@@ -494,5 +511,5 @@ def paged_attn_decode_noalloc(pool: KVPool, q, block_tables, bt_stride, context_
                               num_q_heads, scale, max_context_len, partition_size, out,
                               stream=None) -> None:
     _check(_pycall.paged_attn_decode_noalloc(pool._handle(), q, block_tables, bt_stride,
-                                          context_lens, batch, num_q_heads, scale,
-                                          max_context_len, partition_size, out, stream))
+                                             context_lens, batch, num_q_heads, scale,
+                                             max_context_len, partition_size, out, stream))

@@ -3,7 +3,8 @@
 Every source is compiled for gfx950 only, with packed-fp32 instruction
 selection disabled, and linked into one shared library next to this file;
 ``_pycall``, the CPython extension through which the binding makes its
-per-step calls, is built beside it with the host compiler.
+per-step calls faster, is built beside it where a host compiler and Python's
+headers are there.
 """
 from __future__ import annotations
 
@@ -37,19 +38,26 @@ def hipcc() -> str:
     return path
 
 
-def host_compiler() -> str:
+def host_compiler() -> str | None:
     path = shutil.which("g++") or "/opt/rocm/llvm/bin/clang++"
-    if not os.path.exists(path):
-        raise RuntimeError("no host C++ compiler found")
-    return path
+    return path if os.path.exists(path) else None
 
 
-def build_pycall(verbose: bool = False) -> None:
+def build_pycall(verbose: bool = False) -> bool:
+    """Build the extension; False (and none left behind) without a host
+    compiler or Python's headers: the binding then calls through ctypes."""
+    cc, include = host_compiler(), sysconfig.get_paths()["include"]
+    if cc is None or not os.path.exists(os.path.join(include, "Python.h")):
+        print("note: no host compiler or no Python.h: _pycall is not built, calls go through ctypes", file=sys.stderr)
+        if os.path.exists(PYCALL_PATH):
+            os.remove(PYCALL_PATH)
+        return False
     tmp = PYCALL_PATH + ".tmp"
-    _run([host_compiler(), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden",
-          "-I", sysconfig.get_paths()["include"], "-I", os.path.join(HERE, "..", "include"),
+    _run([cc, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden",
+          "-I", include, "-I", os.path.join(HERE, "..", "include"),
           os.path.join(CSRC, "pycall.cpp"), "-o", tmp], verbose)
     os.replace(tmp, PYCALL_PATH)
+    return True
 
 
 def _run(cmd, verbose):

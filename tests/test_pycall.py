@@ -1,7 +1,13 @@
 """The native calls of the per-step functions give what ctypes gives: the same
 status and message for the same arguments (no GPU: every call here is refused
 or is a no-op), for pointers as None, integers and tensors, and for integers
-that are not Python ints; wrong counts and types raise."""
+that are not Python ints; wrong counts and types raise what ctypes raises, what
+ctypes accepts is accepted, and without the extension the binding is the same."""
+import ctypes
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
@@ -59,6 +65,61 @@ def test_same_status_as_ctypes(name):
     assert refused >= 2
     with pytest.raises(TypeError):
         native(*args[:-1])
-    with pytest.raises(TypeError):
+    with pytest.raises(ctypes.ArgumentError):
         native(*[1.5 if type(a) is int else a for a in args])
     pool.close()
+
+
+# through the public functions, which are the same with and without the extension
+FORMS = """
+import ctypes, sys
+if {hide}:
+    sys.modules["paper_2510_14126_amd._pycall"] = None
+import torch
+from paper_2510_14126_amd import binding as pa
+assert hasattr(pa._pycall, "NAMES") == (not {hide})
+t = torch.zeros(64, dtype=torch.int32)
+pool = pa.kv_pool_create(4, 16, 2, 64, t, t)
+
+class Param:
+    def __init__(self, x):
+        self._as_parameter_ = x
+
+def said(**kw):
+    args = dict(q=t, block_tables=t, bt_stride=4, context_lens=t, batch=0, num_q_heads=8, scale=0.125,
+                max_context_len=50, partition_size=16, out=t, partial_out=t, partial_lse=t)
+    args.update(kw)
+    try:
+        pa.paged_attn_decode(pool, **args)
+        return "accepted"
+    except Exception as e:
+        return f"{{type(e).__module__}}.{{type(e).__name__}}: {{e}}"
+
+for kw in (dict(), dict(batch=1.5), dict(batch="1"), dict(batch=None), dict(scale="x"), dict(scale=None),
+           dict(scale=ctypes.c_float(0.125)), dict(scale=1), dict(batch=ctypes.c_int32(0)),
+           dict(bt_stride=Param(4)), dict(bt_stride=ctypes.c_int32(1)), dict(max_context_len=True), dict(q="12"), dict(q="x"),
+           dict(q=[1]), dict(q=1.5), dict(q=2 ** 70), dict(batch=2 ** 40), dict(stream=torch), dict(scale=1e300)):
+    print(sorted(kw), said(**kw))
+"""
+
+
+def test_accepts_and_raises_as_ctypes_does():
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = [subprocess.run([sys.executable, "-c", FORMS.format(hide=hide)], cwd=root, capture_output=True, text=True)
+           for hide in (False, True)]
+    assert out[0].returncode == 0 and out[1].returncode == 0, out[0].stderr + out[1].stderr
+    native, plain = (x.stdout.splitlines() for x in out)
+    assert native == plain and len(native) == 20
+    assert sum("ctypes.ArgumentError" in x for x in native) >= 4
+    assert sum(x.endswith("accepted") for x in native) >= 6
+
+
+def test_build_without_python_headers(tmp_path, monkeypatch):
+    """The library builds where the extension cannot be: no stale one is left."""
+    from paper_2510_14126_amd import build
+    stale = tmp_path / "_pycall.so"
+    stale.write_bytes(b"")
+    monkeypatch.setattr(build, "PYCALL_PATH", str(stale))
+    monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    assert build.build_pycall() is False
+    assert not stale.exists()
