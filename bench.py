@@ -53,7 +53,7 @@ KERNEL_SOURCES = {
     "cascade": [_CSRC + f for f in ("cascade.hip", "decode_body.h", "shared_body.h", "shared_rows_body.h",
                                     "mfma_body.h", "pa_device.h", "kernels.h")],
     "reduce": [_CSRC + f for f in ("reduce.hip", "pa_device.h", "kernels.h")],
-    "append": [_CSRC + f for f in ("append.hip", "pa_device.h", "kernels.h")],
+    "append": [_CSRC + f for f in ("append.hip", "kernels.h")],
     "extend": [_CSRC + f for f in ("extend.hip", "extend_body.h", "shared_body.h", "mfma_body.h", "pa_device.h",
                                    "kernels.h")],
     "gather_tiles": [_CSRC + f for f in ("gather_tiles.hip", "pa_device.h", "kernels.h")],
