@@ -4,7 +4,6 @@
 #include "kernels.h"
 
 namespace pa {
-hipError_t launch_decode_valu(const DecodeParams&, int, int, bool, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_decode_mfma(const DecodeParams&, bool, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_cascade(const PrefixParams&, const DecodeParams&, int, bool, hipStream_t) {
   return hipErrorNotSupported;

@@ -161,7 +161,7 @@ with open(os.path.join(HERE, "golden", "hand_cases.json")) as f:
     HAND = json.load(f)["cases"]
 
 
-@pytest.mark.parametrize("d,group", [(64, 4), (128, 8)], ids=["valu", "mfma"])
+@pytest.mark.parametrize("d,group", [(64, 4), (128, 8)], ids=["d64_g4", "d128_g8"])
 @pytest.mark.parametrize("case", HAND, ids=[c["name"] for c in HAND])
 def test_hand_cases(case, d, group):
     say(f"hand case {case['name']} D={d} G={group}")

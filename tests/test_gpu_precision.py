@@ -42,7 +42,7 @@ def gated(w, what, S, **kw):
 
 
 @pytest.mark.parametrize("S", [512, 0])
-@pytest.mark.parametrize("hq", [32, 64], ids=["g4_valu", "g8_mfma"])
+@pytest.mark.parametrize("hq", [32, 64], ids=["g4", "g8"])
 def test_near_ties_split_and_single_pass(hq, S):
     ctx = CTX if S else [4099, 513, 16, 1]
     w = near_tie_case(ctx, hq=hq, hkv=8, seed=150)

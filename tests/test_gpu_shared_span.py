@@ -15,6 +15,21 @@ from oracle import compare, decode_workload  # noqa: E402
 from workloads import group_starts, grouped_case, logical_case, page_case  # noqa: E402
 
 
+def split_form(w, partition_size, prefix_len, prefix_partition_size, group_start=None, group_len=0):
+    """The rule of cascade.hip (split_span), restated: whether a step takes the
+    form for small grids (tokens split over the wavefronts, 32 rows each)."""
+    group = w.num_q_heads // w.num_kv_heads
+
+    def tiles(rows):
+        return -(-rows // 32)
+
+    runs = -(-prefix_len // prefix_partition_size) * tiles(w.batch * group)
+    if group_len:
+        runs += (len(group_start) - 1) * tiles(int(np.diff(group_start).max()) * group)
+    runs += -(-(w.max_context_len - prefix_len - group_len) // partition_size) * w.batch
+    return runs * w.num_kv_heads <= 320 + 20 * (max(min(prefix_len, prefix_partition_size), group_len) // 32)
+
+
 def outputs(w, schedule, **kw):
     from paper_2510_14126_amd.device import PagedBatch
     pb = PagedBatch(w, "cuda:0", schedule=schedule, **kw)
@@ -35,9 +50,10 @@ def check(w, what, **kw):
 
 
 @pytest.mark.parametrize("prefix,pps", [(16, 16), (48, 1024), (80, 32), (544, 528), (1040, 1024)])
-@pytest.mark.parametrize("hq,hkv,batch", [(4, 1, 1), (4, 1, 8), (12, 3, 9), (28, 7, 17), (8, 1, 4), (64, 8, 5),
-                                          (32, 8, 90), (64, 8, 40)])   # the last two: 64-row form
-def test_prefix_tiles(hq, hkv, batch, prefix, pps):
+@pytest.mark.parametrize("hq,hkv,batch,split", [(4, 1, 1, True), (4, 1, 8, True), (12, 3, 9, True), (28, 7, 17, True),
+                                                (8, 1, 4, True), (64, 8, 5, True), (32, 8, 90, False),
+                                                (64, 8, 56, False)])
+def test_prefix_tiles(hq, hkv, batch, split, prefix, pps):
     rng = np.random.default_rng(700 + batch)
     ctx = prefix + rng.integers(1, 70, size=batch)
     w = page_case(logical_case(701 + batch, batch, hq, hkv, 128, ctx, prefix_len=prefix), 702, poison=True)
@@ -45,8 +61,9 @@ def test_prefix_tiles(hq, hkv, batch, prefix, pps):
         w.context_lens[2] = 5
         w.context_lens[1] = 0
         w.context_lens[3] = prefix - 1
-    check(w, f"Hq={hq} Hkv={hkv} batch={batch} prefix={prefix}/{pps}", partition_size=64, prefix_len=prefix,
-          prefix_partition_size=pps)
+    kw = dict(partition_size=64, prefix_len=prefix, prefix_partition_size=pps)
+    assert split_form(w, **kw) == split
+    check(w, f"Hq={hq} Hkv={hkv} batch={batch} prefix={prefix}/{pps}", **kw)
 
 
 @pytest.mark.parametrize("scale", [-0.15, 0.0])
