@@ -1,12 +1,13 @@
 // One-launch shared-prefix (cascade) step: some workgroups run the
 // shared-prefix pass (matrix-core tiles over all query rows) and, with a
 // second level, the pass over each group's shared tokens (tiles over the
-// group's rows), in one of two forms (split_span); the others run the per-sequence decode over the tokens
-// after what is shared.  All write disjoint (o, lse) partials, so they need
-// no synchronisation.  Shared and per-sequence work
-// alternate in runs of num_kv_heads workgroups (with a phase flip every 8
-// runs, see below), so every CU holds some of each at once: the L2-fed prefix work overlaps the HBM-fed per-sequence work
-// instead of preceding it, and workgroup i still serves KV head
+// group's rows), in one of two forms (split_span); the others run the
+// per-sequence decode over the tokens after what is shared.  All write
+// disjoint (o, lse) partials, so they need no synchronisation.  Shared and
+// per-sequence work alternate in runs of num_kv_heads workgroups (with a phase
+// flip every 8 runs, see below), so every CU holds some of each at once: the
+// L2-fed prefix work overlaps the HBM-fed per-sequence work instead of
+// preceding it, and workgroup i still serves KV head
 // i % num_kv_heads, which keeps each head on one XCD (the dispatcher deals
 // workgroups to the XCDs round-robin).
 #include "decode_body.h"
@@ -45,12 +46,12 @@ cascade_kernel(const PrefixParams pp, const DecodeParams dp, int prefix_runs, in
   const int both = min(shared_runs, decode_runs);
   bool shared;
   int idx;
-    if ((SPLIT ? 1 : 3) * shared_runs >= decode_runs) {
-    // Shared work at least a third of the decode runs (the fixer batch with
-    // its request groups): all shared runs first measured 2% faster than
-    // interleaving them; a run of consecutive shared runs reaches every
-    // shader engine.  (Split spans: as many shared runs as decode runs; with a
-    // third, 51.2 -> 54.7 us on the same batch.)
+  if ((SPLIT ? 1 : 3) * shared_runs >= decode_runs) {
+    // Many shared runs: all of them first; consecutive ones reach every shader
+    // engine.  Rows form, from a third of the decode runs on: 2% faster than
+    // interleaving on the fixer batch with its request groups.  Split form, whose
+    // runs are twice as many and shorter, from as many as decode runs on: with a
+    // third, 51.2 -> 54.7 us on the same batch.
     shared = run < shared_runs;
     idx = shared ? run : run - shared_runs;
   } else if (run < 2 * both) {

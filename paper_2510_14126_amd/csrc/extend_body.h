@@ -55,13 +55,14 @@ namespace extend {
 
 using mfma::bf16x8_t;
 using mfma::floatx16_t;
-using mfma::kLazyRescale;
 using mfma::kWaves;
-using mfma::lds_floatx4_t;
 using mfma::lds_short4_t;
 using mfma::lds_u32x4_t;
 using mfma::pack_bf16;
 using mfma::u32x4_t;
+using shared::k_off;     // K rows of a stage; lane (h, n) reads row n, chunk 2s + h
+using shared::per_row;
+using shared::raise_max;
 
 typedef int i32x2_t __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) i32x2_t lds_i32x2_t;
@@ -78,12 +79,6 @@ constexpr int kRowOffset = kIdOffset + kExtendMaxTokens / 16 * 4;   // one value
 constexpr int kLdsBytes = kRowOffset + kWaves * kRows * 4;
 
 template <bool B> struct BoolTag { static constexpr bool value = B; };
-
-// LDS byte offset of 16-byte chunk c of token row r (0..31) in a staged K
-// tile: chunk c at position c ^ (r % 16).  Writers fill whole rows; readers
-// (lane (h, n): row n, chunk 2s + h) touch eight distinct positions modulo
-// eight in every eight consecutive lanes.
-__device__ __forceinline__ int k_off(int r, int c) { return r * (2 * kD) + ((c ^ (r & 15)) << 4); }
 
 // LDS byte offset of 16-byte chunk c of token row r in a staged V tile: eight
 // 32-byte windows (dims 16w .. 16w+15) per row, window w at position
@@ -235,20 +230,7 @@ __device__ __forceinline__ void extend_body(const ExtendParams& p, int wg_index,
 #pragma unroll
     for (int i = 0; i < 16; ++i) o[j][i] = 0.f;
 
-  // One value per query row, from the lane that holds it as column n, to the
-  // lanes that hold the row's outputs: rows 8a + 4h + b in rowv[4a + b].
   lds_f32_t* rowv = reinterpret_cast<lds_f32_t*>(smem + kRowOffset) + wave * kRows;
-  auto per_row = [&](float x, float (&out)[16]) {
-    if (h == 0) rowv[n] = x;
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const mfma::floatx4_t y = *reinterpret_cast<const lds_floatx4_t*>(rowv + 8 * a + 4 * h);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) out[4 * a + e] = y[e];
-    }
-    __builtin_amdgcn_wave_barrier();
-  };
 
   // Running-max test of a stage whose first token is t0, before its
   // probabilities are formed.
@@ -258,26 +240,8 @@ __device__ __forceinline__ void extend_body(const ExtendParams& p, int wg_index,
 #pragma unroll
     for (int r = 0; r < 16; ++r)
       if (!TAIL || t0 + 8 * (r >> 2) + 4 * h + (r & 3) < lim) mx = fmaxf(mx, a[r]);
-    const float xmax = mx * scale;   // NaN when all are masked and the scale is 0
-    if (__builtin_amdgcn_ballot_w64(xmax > m + kLazyRescale) != 0) {
-      float x = xmax, y = xmax;
-      swap32(x, y);
-      const float bm = fmaxf(x, y);
-      const float mn = bm > m + kLazyRescale ? bm : m;
-      // 1 for rows that keep their max (or have attended to nothing yet)
-      const float alpha = mn == -__builtin_inff() ? 1.f : fast_exp2(m - mn);
-      l *= alpha;
-      if (__builtin_amdgcn_ballot_w64(m != -__builtin_inff()) != 0) {
-        float ar[16];
-        per_row(alpha, ar);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) o[j][r] *= ar[r];
-      }
-      m = mn;
-      neg = mn == -__builtin_inff() ? 0.f : -mn;
-    }
+    // NaN (no rescale) when all are masked and the scale is 0
+    raise_max(mx * scale, m, neg, l, o, rowv, h, n);
   };
 
   // Probabilities of stage j (raw scores a, first token t0) and their PV.
@@ -379,7 +343,7 @@ __device__ __forceinline__ void extend_body(const ExtendParams& p, int wg_index,
   swap32(lx, ly);
   const float lcol = lx + ly;
   float inv[16];
-  per_row(lcol > 0.f ? 1.0f / lcol : 0.f, inv);
+  per_row(rowv, h, n, lcol > 0.f ? 1.0f / lcol : 0.f, inv);
   lds_u8_t* tile = smem + wave * (kRows * kD * 2);
 #pragma unroll
   for (int r = 0; r < 16; ++r) {

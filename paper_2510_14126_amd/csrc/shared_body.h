@@ -74,6 +74,47 @@ __device__ __forceinline__ int a_row(int i) {
   return 16 * (a >> 1) + 2 * (4 * (a & 1) + b) + h;
 }
 
+// One value per row, from the lane (h, n) that holds it as column n, to the lanes
+// that hold the row's outputs: rows 8a + 4h + b in out[4a + b].  rowv: 32 floats
+// of LDS of the wavefront's own.
+__device__ __forceinline__ void per_row(lds_f32_t* rowv, int h, int n, float x, float (&out)[16]) {
+  if (h == 0) rowv[n] = x;
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    const floatx4_t y = *reinterpret_cast<const lds_floatx4_t*>(rowv + 8 * a + 4 * h);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) out[4 * a + e] = y[e];
+  }
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Running-max step before a stage's probabilities: xmax is the lane's largest
+// unmasked score of column n.  The test needs no cross-lane reduction: any lane
+// above its row's max + kLazyRescale triggers the rescale.
+__device__ __forceinline__ void raise_max(float xmax, float& m, float& neg, float& l, floatx16_t (&o)[4],
+                                          lds_f32_t* rowv, int h, int n) {
+  if (__builtin_amdgcn_ballot_w64(xmax > m + kLazyRescale) != 0) {
+    float x = xmax, y = xmax;
+    swap32(x, y);
+    const float bm = fmaxf(x, y);
+    const float mn = bm > m + kLazyRescale ? bm : m;
+    // 1 for rows that keep their max (or have attended to nothing yet)
+    const float alpha = mn == -__builtin_inff() ? 1.f : fast_exp2(m - mn);
+    l *= alpha;
+    if (__builtin_amdgcn_ballot_w64(m != -__builtin_inff()) != 0) {
+      float ar[16];
+      per_row(rowv, h, n, alpha, ar);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[j][r] *= ar[r];
+    }
+    m = mn;
+    neg = mn == -__builtin_inff() ? 0.f : -mn;
+  }
+}
+
 // The rows of one tile against nblk blocks, on all wavefronts of the workgroup.
 //   q_row    query row (128 bf16) of column n
 //   desc(base, i)  buffer descriptor of the tile at block i (i < nblk) of the
@@ -141,19 +182,6 @@ __device__ __forceinline__ void tile_core(const uint16_t* q_row, const uint16_t*
   lds_f32_t* sm = reinterpret_cast<lds_f32_t*>(smem + kStatOffset);   // [kWaves][32]
   lds_f32_t* sl = sm + kWaves * kRows;                                 // [kWaves][32]
   lds_f32_t* rowv = sl + kWaves * kRows + wave * kRows;
-  // One value per row, from the lane that holds it as column n, to the lanes
-  // that hold the row's outputs: rows 8a + 4h + b in out[4a + b].
-  auto per_row = [&](float x, float (&out)[16]) {
-    if (h == 0) rowv[n] = x;
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const floatx4_t y = *reinterpret_cast<const lds_floatx4_t*>(rowv + 8 * a + 4 * h);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) out[4 * a + e] = y[e];
-    }
-    __builtin_amdgcn_wave_barrier();
-  };
 
   float m = -__builtin_inff(), neg = 0.f, l = 0.f;
   floatx16_t o[4];
@@ -195,31 +223,10 @@ __device__ __forceinline__ void tile_core(const uint16_t* q_row, const uint16_t*
         if (2 * (r & 7) + h >= see[r >> 3]) a[r] = -__builtin_inff();
     }
 
-    // The rescale test needs no cross-lane reduction: any lane above its
-    // row's max + kLazyRescale triggers it.
     float mx = a[0];
 #pragma unroll
     for (int r = 1; r < 16; ++r) mx = fmaxf(mx, a[r]);
-    const float xmax = mx * scale;
-    if (__builtin_amdgcn_ballot_w64(xmax > m + kLazyRescale) != 0) {
-      float x = xmax, y = xmax;
-      swap32(x, y);
-      const float bm = fmaxf(x, y);
-      const float mn = bm > m + kLazyRescale ? bm : m;
-      // 1 for rows that keep their max (or have attended to nothing yet)
-      const float alpha = mn == -__builtin_inff() ? 1.f : fast_exp2(m - mn);
-      l *= alpha;
-      if (__builtin_amdgcn_ballot_w64(m != -__builtin_inff()) != 0) {
-        float ar[16];
-        per_row(alpha, ar);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) o[j][r] *= ar[r];
-      }
-      m = mn;
-      neg = mn == -__builtin_inff() ? 0.f : -mn;
-    }
+    raise_max(mx * scale, m, neg, l, o, rowv, h, n);
 
     u32x4_t hi[2], lo[2];
     float sum[2];
@@ -286,7 +293,7 @@ __device__ __forceinline__ void tile_core(const uint16_t* q_row, const uint16_t*
   const float inv = lt > 0.f ? 1.0f / lt : 0.f;
   if (wave == 0) stats(mx, lt);
   float f[16];
-  per_row(fast_exp2(m - mref) * inv, f);
+  per_row(rowv, h, n, fast_exp2(m - mref) * inv, f);
   auto piece = [&](int d, int b) {   // the lane's dims of row 8d + 4h + b, normalised
     return floatx4_t{o[0][4 * d + b] * f[4 * d + b], o[1][4 * d + b] * f[4 * d + b],
                      o[2][4 * d + b] * f[4 * d + b], o[3][4 * d + b] * f[4 * d + b]};

@@ -27,13 +27,12 @@ namespace mfma {
 
 constexpr int kD = 128;
 
-// Online-softmax state of NT column tiles (16 query columns each).
-template <int NT>
+// Online-softmax state of the wavefront's 16 query columns.
 struct MfmaState {
-  float m[NT];        // running max of query column n (log2 units), same in all groups
-  float neg[NT];      // -m, or 0 while m is -inf
-  float l[NT];        // this lane's share of the column sum (tokens 4q..4q+3 of each block)
-  floatx4_t o[NT][8]; // [j]: O[rows 4q+r][dim 16j + n]
+  float m;            // running max of query column n (log2 units), same in all groups
+  float neg;          // -m, or 0 while m is -inf
+  float l;            // this lane's share of the column sum (tokens 4q..4q+3 of each block)
+  floatx4_t o[8];     // [j]: O[rows 4q+r][dim 16j + n]
 };
 
 // Window position of row r in a staged V tile: v_swz(r) = (r ^ r/4) & 7.
@@ -73,8 +72,7 @@ constexpr int kPrefixRing = 4;
 static_assert(kPrefixRing == 2 * kPrefixStageBlocks, "two pairs of slots");
 
 // NB 16-token blocks (NB even) staged at st + b * kPrefixStageBytes (K in the
-// k_stage layout, V in the v_stage layout) against NT column tiles, which
-// share every K and V operand read from LDS.  The
+// k_stage layout, V in the v_stage layout) against the wavefront's columns.  The
 // QK^T of every block comes first (independent MFMA chains); lane (q, n)
 // then holds the scores of tokens 4r+q of each block for column n, and one
 // online-softmax step covers all NB*16 tokens.  For PV, blocks 2p and 2p+1
@@ -84,21 +82,20 @@ static_assert(kPrefixRing == 2 * kPrefixStageBlocks, "two pairs of slots");
 // per 16 output dims (output column n = dim 16j + n), whose B operand two
 // transposing LDS reads deliver straight from the staged V tiles (vtr is
 // the lane's v_tr offset).  valid[b]: rows of block b that hold tokens of the
-// span (0: an empty block); lim[t][b]: rows of block b that column n of
-// tile t may see.  Rows past valid[b] are zeroed in the B operand (their V may be
+// span (0: an empty block); lim[b]: rows of block b that column n
+// may see.  Rows past valid[b] are zeroed in the B operand (their V may be
 // anything, NaN included).  scale_log2 >= 0: the scale is applied inside the
 // exponent's FMA, and the running-max test uses the lane's largest unmasked
 // raw score times the scale (the same value as the largest scaled score,
 // since multiplying by a non-negative number keeps the order).
-template <bool TAIL, int NB, int NT>
-__device__ __forceinline__ void tile_core_nb(MfmaState<NT>& S, const lds_u8_t* st, int vtr,
-                                             const uint4 (&qb)[NT][4], const int (&valid)[NB],
-                                             const int (&lim)[NT][NB], int q, int n, float scale_log2) {
+template <bool TAIL, int NB>
+__device__ __forceinline__ void tile_core_nb(MfmaState& S, const lds_u8_t* st, int vtr, const uint4 (&qb)[4],
+                                             const int (&valid)[NB], const int (&lim)[NB], int q, int n,
+                                             float scale_log2) {
   static_assert(NB % 2 == 0, "blocks go in pairs through the PV contraction");
   const floatx4_t z = {0.f, 0.f, 0.f, 0.f};
-  // K operands of every block first (shared by the NT tiles), then the score
-  // MFMAs interleaved over tiles and blocks so that consecutive MFMAs do not
-  // depend on each other.
+  // K operands of every block first, then the score MFMAs interleaved over the
+  // blocks so that consecutive MFMAs do not depend on each other.
   u32x4_t ka[NB][4];
 #pragma unroll
   for (int b = 0; b < NB; ++b)
@@ -106,87 +103,68 @@ __device__ __forceinline__ void tile_core_nb(MfmaState<NT>& S, const lds_u8_t* s
     for (int c = 0; c < 4; ++c)
       ka[b][c] = *reinterpret_cast<const lds_u32x4_t*>(st + b * kPrefixStageBytes + k_stage(k_arow(n), 4 * c + q));
   __builtin_amdgcn_s_setprio(1);
-  floatx4_t a[NT][NB];
+  floatx4_t a[NB];
 #pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-      a[t][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ka[b][0]),
-                                                        __builtin_bit_cast(bf16x8_t, qb[t][0]), z, 0, 0, 0);
+  for (int b = 0; b < NB; ++b)
+    a[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ka[b][0]),
+                                                   __builtin_bit_cast(bf16x8_t, qb[0]), z, 0, 0, 0);
 #pragma unroll
   for (int c = 1; c < 4; ++c)
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-      for (int b = 0; b < NB; ++b)
-        a[t][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ka[b][c]),
-                                                          __builtin_bit_cast(bf16x8_t, qb[t][c]), a[t][b], 0, 0, 0);
+    for (int b = 0; b < NB; ++b)
+      a[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ka[b][c]),
+                                                     __builtin_bit_cast(bf16x8_t, qb[c]), a[b], 0, 0, 0);
   __builtin_amdgcn_s_setprio(0);
 
-  // One rescale branch for all tiles: it is rare, and what follows it is
-  // straight-line code that the scheduler can interleave across tiles.
-  float xmax[NT];   // NaN when all are masked and the scale is 0
-  bool raise = false;
+  float mx = -__builtin_inff();   // the lane's largest unmasked raw score
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    float mx = -__builtin_inff();   // the lane's largest unmasked raw score
+  for (int b = 0; b < NB; ++b)
 #pragma unroll
-    for (int b = 0; b < NB; ++b)
+    for (int r = 0; r < 4; ++r)
+      if (!TAIL || 4 * r + q < lim[b]) mx = fmaxf(mx, a[b][r]);
+  const float xmax = mx * scale_log2;   // NaN when all are masked and the scale is 0
+  if (__builtin_amdgcn_ballot_w64(xmax > S.m + kLazyRescale) != 0) {   // rare
+    const float bm = group_max4(xmax);
+    const float mn = bm > S.m + kLazyRescale ? bm : S.m;
+    // 1 for columns that keep their max (or have attended to nothing yet)
+    const float alpha = mn == -__builtin_inff() ? 1.f : fast_exp2(S.m - mn);
+    S.l *= alpha;
+    S.m = mn;
+    S.neg = mn == -__builtin_inff() ? 0.f : -mn;
+    float ar[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (!TAIL || 4 * r + q < lim[t][b]) mx = fmaxf(mx, a[t][b][r]);
-    xmax[t] = mx * scale_log2;
-    raise |= xmax[t] > S.m[t] + kLazyRescale;
-  }
-  if (__builtin_amdgcn_ballot_w64(raise) != 0) {
+    for (int r = 0; r < 4; ++r) ar[r] = column_value(alpha, q, r);
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const float bm = group_max4(xmax[t]);
-      const float mn = bm > S.m[t] + kLazyRescale ? bm : S.m[t];
-      // 1 for columns that keep their max (or have attended to nothing yet)
-      const float alpha = mn == -__builtin_inff() ? 1.f : fast_exp2(S.m[t] - mn);
-      S.l[t] *= alpha;
-      S.m[t] = mn;
-      S.neg[t] = mn == -__builtin_inff() ? 0.f : -mn;
-      float ar[4];
+    for (int blk = 0; blk < 8; ++blk)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) ar[r] = column_value(alpha, q, r);
-#pragma unroll
-      for (int blk = 0; blk < 8; ++blk)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) S.o[t][blk][r] *= ar[r];
-    }
+      for (int r = 0; r < 4; ++r) S.o[blk][r] *= ar[r];
   }
 
-  // Probabilities of tile t as bf16 pairs (the A operands: element e of
-  // pa[t][p] and pl[t][p] is the high and low part of the weight of score
-  // 8p + e, p = hi + lo to about 2^-17 relative); the column sum adds the fp32
-  // values.
-  u32x4_t pa[NT][NB / 2], pl[NT][NB / 2];
+  // Probabilities as bf16 pairs (the A operands: element e of pa[p] and pl[p]
+  // is the high and low part of the weight of score 8p + e, p = hi + lo to about
+  // 2^-17 relative); the column sum adds the fp32 values.
+  u32x4_t pa[NB / 2], pl[NB / 2];
+  float sum = 0.f;
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    float sum = 0.f;
+  for (int pp = 0; pp < NB / 2; ++pp) {
 #pragma unroll
-    for (int pp = 0; pp < NB / 2; ++pp) {
+    for (int e = 0; e < 8; e += 2) {
+      float pf[2];
 #pragma unroll
-      for (int e = 0; e < 8; e += 2) {
-        float pf[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          // element e + i is token 4((e+i) % 4) + q of block 2pp + (e+i) / 4
-          const int b = 2 * pp + ((e + i) >> 2), r = (e + i) & 3;
-          float ex = fmaf(a[t][b][r], scale_log2, S.neg[t]);
-          if (TAIL && 4 * r + q >= lim[t][b]) ex = -__builtin_inff();
-          pf[i] = fast_exp2(ex);
-        }
-        const uint32_t hi = pack_bf16(pf[0], pf[1]);
-        pa[t][pp][e / 2] = hi;
-        pl[t][pp][e / 2] = pack_bf16(pf[0] - bf16_lo(hi), pf[1] - bf16_hi(hi));
-        sum += pf[0] + pf[1];
+      for (int i = 0; i < 2; ++i) {
+        // element e + i is token 4((e+i) % 4) + q of block 2pp + (e+i) / 4
+        const int b = 2 * pp + ((e + i) >> 2), r = (e + i) & 3;
+        float ex = fmaf(a[b][r], scale_log2, S.neg);
+        if (TAIL && 4 * r + q >= lim[b]) ex = -__builtin_inff();
+        pf[i] = fast_exp2(ex);
       }
+      const uint32_t hi = pack_bf16(pf[0], pf[1]);
+      pa[pp][e / 2] = hi;
+      pl[pp][e / 2] = pack_bf16(pf[0] - bf16_lo(hi), pf[1] - bf16_hi(hi));
+      sum += pf[0] + pf[1];
     }
-    S.l[t] += sum;
   }
+  S.l += sum;
 
   // Element e of a block's B words is its token 4e + q.
   uint32_t mlo[NB], mhi[NB];
@@ -199,14 +177,13 @@ __device__ __forceinline__ void tile_core_nb(MfmaState<NT>& S, const lds_u8_t* s
       mhi[b] = (q + 8 < valid[b] ? 0xffffu : 0u) | (q + 12 < valid[b] ? 0xffff0000u : 0u);
     }
   }
-  // Each B operand (two transposing reads) serves the NT tiles.  The operands
-  // of kPvGroup output columns are read together and their high-part MFMAs
-  // issued before the low-part ones, so that no MFMA waits for its own LDS
-  // read or for the MFMA just before it; the MFMAs run at raised priority, so
-  // that a wavefront in its softmax does not hold them up.  (64-call
-  // generator step, one wavefront per SIMD in this pass: groups of 1 / 2 / 4
-  // columns 24.9 / 24.4 / 24.3 us, and with the priority 24.6 / 24.5 / 23.9;
-  // before, 25.1.)
+  // The B operands (two transposing reads each) of kPvGroup output columns are
+  // read together and their high-part MFMAs issued before the low-part ones, so
+  // that no MFMA waits for its own LDS read or for the MFMA just before it; the
+  // MFMAs run at raised priority, so that a wavefront in its softmax does not
+  // hold them up.  (64-call generator step, one wavefront per SIMD in this pass:
+  // groups of 1 / 2 / 4 columns 24.9 / 24.4 / 24.3 us, and with the priority
+  // 24.6 / 24.5 / 23.9; before, 25.1.)
   constexpr int kPvGroup = 4;
   __builtin_amdgcn_s_setprio(1);
 #pragma unroll
@@ -228,23 +205,16 @@ __device__ __forceinline__ void tile_core_nb(MfmaState<NT>& S, const lds_u8_t* s
       }
 #pragma unroll
       for (int i = 0; i < kPvGroup; ++i)
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-          S.o[t][j + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pa[t][pp]),
-                                                                  __builtin_bit_cast(bf16x8_t, vb[i]),
-                                                                  S.o[t][j + i], 0, 0, 0);
+        S.o[j + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pa[pp]),
+                                                             __builtin_bit_cast(bf16x8_t, vb[i]), S.o[j + i], 0, 0, 0);
 #pragma unroll
       for (int i = 0; i < kPvGroup; ++i)
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-          S.o[t][j + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pl[t][pp]),
-                                                                  __builtin_bit_cast(bf16x8_t, vb[i]),
-                                                                  S.o[t][j + i], 0, 0, 0);
+        S.o[j + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pl[pp]),
+                                                             __builtin_bit_cast(bf16x8_t, vb[i]), S.o[j + i], 0, 0, 0);
     }
   }
   __builtin_amdgcn_s_setprio(0);
 }
-
 
 // Attention over the prefix that every sequence of the batch shares: for KV
 // head g the B*G query rows form the columns of dense 16-row tiles (four
@@ -298,7 +268,7 @@ __device__ __forceinline__ void shared_span_body(const PrefixParams& p, int g, c
   // is the negation of every score): the core needs a non-negative one.
   const uint32_t qflip = p.scale_log2 < 0.f ? 0x80008000u : 0u;
   const float scale_abs = fabsf(p.scale_log2);
-  uint4 qb[1][4];
+  uint4 qb[4];
   int ctx;
   int min_ctx;
   {
@@ -310,7 +280,7 @@ __device__ __forceinline__ void shared_span_body(const PrefixParams& p, int g, c
     for (int s = 0; s < 4; ++s) {
       uint4 w = ok ? *reinterpret_cast<const uint4*>(qrow + (4 * s + q) * 8) : make_uint4(0, 0, 0, 0);
       w.x ^= qflip; w.y ^= qflip; w.z ^= qflip; w.w ^= qflip;
-      qb[0][s] = w;
+      qb[s] = w;
     }
     int c = ok ? p.context_lens[bR] : 0;
     c = c < 0 ? 0 : (c > p.max_ctx ? p.max_ctx : c);
@@ -319,12 +289,12 @@ __device__ __forceinline__ void shared_span_body(const PrefixParams& p, int g, c
     min_ctx = __builtin_amdgcn_readfirstlane(-(int)group_max4(row_max16(-(float)c)));
   }
 
-  MfmaState<1> S;
-  S.m[0] = -__builtin_inff();
-  S.neg[0] = 0.f;
-  S.l[0] = 0.f;
+  MfmaState S;
+  S.m = -__builtin_inff();
+  S.neg = 0.f;
+  S.l = 0.f;
 #pragma unroll
-  for (int blk = 0; blk < 8; ++blk) S.o[0][blk] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  for (int blk = 0; blk < 8; ++blk) S.o[blk] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 
   constexpr size_t kTileElems = 16 * kD;
   const size_t blk_stride = (size_t)p.num_kv_heads * kTileElems;
@@ -379,7 +349,7 @@ __device__ __forceinline__ void shared_span_body(const PrefixParams& p, int g, c
         load(ring[(2 * h + kRing - 2) % kRing], 2 * j + kRing - 2);
         load(ring[(2 * h + kRing - 1) % kRing], 2 * j + kRing - 1);
         __syncthreads();
-        int valid[NB], lim[1][NB];
+        int valid[NB], lim[NB];
         bool fast = true;
 #pragma unroll
         for (int s = 0; s < NB; ++s) {
@@ -387,7 +357,7 @@ __device__ __forceinline__ void shared_span_body(const PrefixParams& p, int g, c
           const bool has = i < nblk;
           const int tb = has ? start + block_of(i) * 16 : end;
           valid[s] = has ? min(16, end - tb) : 0;
-          lim[0][s] = min(valid[s], max(ctx - tb, 0));
+          lim[s] = min(valid[s], max(ctx - tb, 0));
           fast = fast && valid[s] == 16 && min_ctx - tb >= 16;
           if constexpr (TRACE) {
             // slot = the block's position in the span (not in the walk)
@@ -411,12 +381,12 @@ __device__ __forceinline__ void shared_span_body(const PrefixParams& p, int g, c
 
   // Normalise per row and write this partition's partials: lane (q, n)
   // holds O[rows 4q+r][dims 16j + n], j = 0..7.
-  const float lcol = group_sum4(S.l[0]);
+  const float lcol = group_sum4(S.l);
   const float inv = lcol > 0.f ? 1.0f / lcol : 0.f;
   if (q == 0 && row0 + n < total_rows) {
     const int R = row0 + n;
     const size_t row = ((size_t)(sp.seq0 + R / G) * p.num_q_heads + g * G + R % G) * p.part_stride + part;
-    p.part_lse[row] = lcol > 0.f ? (S.m[0] + log2f(lcol)) * kLn2 : -__builtin_inff();
+    p.part_lse[row] = lcol > 0.f ? (S.m + log2f(lcol)) * kLn2 : -__builtin_inff();
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
@@ -427,7 +397,7 @@ __device__ __forceinline__ void shared_span_body(const PrefixParams& p, int g, c
           ((size_t)(sp.seq0 + R / G) * p.num_q_heads + g * G + R % G) * p.part_stride + part;
       float* po = p.part_o + row * kD + n;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) store_partial(po + 16 * j, S.o[0][j][r] * f);
+      for (int j = 0; j < 8; ++j) store_partial(po + 16 * j, S.o[j][r] * f);
     }
   }
 }
