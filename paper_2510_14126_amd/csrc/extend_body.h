@@ -31,10 +31,11 @@
 // MFMAs and about 115 VALU instructions per wavefront and stage.  The prefill
 // of 93 sequences (55k chunk tokens over 2.4k-3.3k contexts, four heads per KV
 // head) takes 20% fewer cycles than with 16x16 tiles and the unpipelined loop
-// (5.2e7 against 6.6e7 GPU cycles; 3.53 -> 3.15-3.3 ms, 660 -> 704-740
-// TFLOP/s of causal flops, 1.5 times that on the matrix cores), and runs at
-// 1.75 instead of 1.96 GHz: the power limit holds it now (a 16384^3 library
-// matrix product reaches 1339 TFLOP/s here).  Two tiles per wavefront at one
+// (5.2e7 against 6.6e7 GPU cycles summed over the XCDs; 3.52 -> 3.18-3.35 ms, 660
+// -> 694-732 TFLOP/s of causal flops, 1.5 times that on the matrix cores), and runs
+// at 1.99 instead of 2.35 GHz, drawing 1.36 kW either way: the card's 1.4 kW limit
+// holds it (a 16384^3 library matrix product reaches 1340-1350 TFLOP/s here, at 1.82
+// GHz and 1.37 kW).  Two tiles per wavefront at one
 // wavefront per SIMD, which halve the LDS reads, measured 4.5 ms; the low
 // parts formed by v_dot2 instead of unpack and subtract 3.32 against 3.15 ms;
 // raised priority during the MFMAs 3.21 against 3.15 ms.
