@@ -8,7 +8,7 @@ namespace {
 
 using mfma::kWaves;
 
-// Tiles kept in flight per wavefront.  With every tile read once from memory
+// Tiles kept in flight per wavefront (DEEP: see deep_ring).  With every tile read once from memory
 // (STREAM) at D = 128, three tiles and two wavefronts per SIMD: 256 sequences
 // of 64..8192 tokens take 238 us, against 251 us with two tiles and three
 // wavefronts.  Where sequences share blocks the tiles come from L2, the items
@@ -20,14 +20,14 @@ using mfma::kWaves;
 // 28.6 / 28.2 us, 256 of 256 27.8 / 25.3 / 23.2, 64 over a shared 2048-token
 // prefix 24.6 / 23.3 / 21.5, 256 of 64..8192 in 512-token partitions 413 / 397 /
 // 383 (VALU kernel 407), in one partition 391 / 394 / 386.
-template <int D, bool STREAM>
-constexpr int nbuf() { return D == 128 && STREAM ? 3 : 2; }
+template <int D, bool STREAM, bool DEEP>
+constexpr int nbuf() { return DEEP ? 4 : D == 128 && STREAM ? 3 : 2; }
 
-template <int D, int G, bool TRACE, bool STREAM, bool APPEND, bool ONE_MERGE>
+template <int D, int G, bool TRACE, bool STREAM, bool APPEND, bool ONE_MERGE, bool DEEP>
 __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, ONE_MERGE && G == 8 ? 2 : 8)))
 decode_mfma_kernel(const DecodeParams p) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[decode::lds_bytes<D, G, STREAM>()];
-  decode::decode_body<D, G, nbuf<D, STREAM>(), TRACE, STREAM, APPEND, ONE_MERGE>(p, blockIdx.x, (lds_u8_t*)smem);
+  decode::decode_body<D, G, nbuf<D, STREAM, DEEP>(), TRACE, STREAM, APPEND, ONE_MERGE>(p, blockIdx.x, (lds_u8_t*)smem);
 }
 
 // Whether one wavefront merges and stores an item's rows, and at G = 8 two
@@ -46,6 +46,19 @@ bool one_merge(const DecodeParams& p) {
          (int64_t)p.num_parts * p.batch * p.num_kv_heads >= 16384;
 }
 
+// Whether the wavefronts keep four tiles in flight at D = 64: where every
+// workgroup has a CU to itself and an item is long, a wavefront's own round trips
+// are its time, and the loads past its end are few.  Whole step, two / four
+// tiles, four heads per KV head: 3 sequences of 12.7K-20.8K tokens on one KV head
+// in 2048-token partitions (33 workgroups) 21.6 / 19.8 us; 16 of 8K, 128 workgroups of
+// 2048 tokens 24.5 / 22.2, 256 of 512 11.0 / 10.7.  The other side: 288 workgroups of
+// 2048 tokens 32.0 / 35.4, 128 of 256 tokens 7.8 / 8.0; with the default cache policy
+// (half of the tokens shared) 256 of 512 tokens 9.0 / 9.3, 224 of 1024 the same.
+constexpr int64_t kDeepMaxWorkgroups = 256;   // one per CU
+bool deep_ring(const DecodeParams& p, int64_t grid) {
+  return p.head_dim == 64 && grid <= kDeepMaxWorkgroups && p.part_tokens >= (p.stream_tiles ? 512 : 1024);
+}
+
 // The trace kernel keeps the default cache policy (the hint changes no
 // index) and has no fused append.
 template <int D, int G>
@@ -56,20 +69,24 @@ hipError_t launch_t(const DecodeParams& p, bool trace, hipStream_t stream) {
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * kWaves), 0, stream, p);
   };
+  constexpr bool kDeep = D == 64, kOneMerge = D == 128;
+  const bool deep = deep_ring(p, grid);
   if (trace)
-    go(decode_mfma_kernel<D, G, true, false, false, false>);
+    go(decode_mfma_kernel<D, G, true, false, false, false, false>);
   else if (p.stream_tiles && append)
-    go(decode_mfma_kernel<D, G, false, true, true, false>);
+    go(deep ? decode_mfma_kernel<D, G, false, true, true, false, kDeep>
+            : decode_mfma_kernel<D, G, false, true, true, false, false>);
   else if (p.stream_tiles)
-    go(decode_mfma_kernel<D, G, false, true, false, false>);
-  else if (one_merge(p) && append)
-    go(decode_mfma_kernel<D, G, false, false, true, D == 128>);
-  else if (one_merge(p))
-    go(decode_mfma_kernel<D, G, false, false, false, D == 128>);
+    go(deep ? decode_mfma_kernel<D, G, false, true, false, false, kDeep>
+            : decode_mfma_kernel<D, G, false, true, false, false, false>);
   else if (append)
-    go(decode_mfma_kernel<D, G, false, false, true, false>);
+    go(one_merge(p) ? decode_mfma_kernel<D, G, false, false, true, kOneMerge, false>
+       : deep       ? decode_mfma_kernel<D, G, false, false, true, false, kDeep>
+                    : decode_mfma_kernel<D, G, false, false, true, false, false>);
   else
-    go(decode_mfma_kernel<D, G, false, false, false, false>);
+    go(one_merge(p) ? decode_mfma_kernel<D, G, false, false, false, kOneMerge, false>
+       : deep       ? decode_mfma_kernel<D, G, false, false, false, false, kDeep>
+                    : decode_mfma_kernel<D, G, false, false, false, false, false>);
   return hipGetLastError();
 }
 
