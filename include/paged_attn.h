@@ -124,8 +124,9 @@ int kv_pool_num_free(const pa_kv_pool *pool, int32_t *n_out);
 int kv_pool_refcount(const pa_kv_pool *pool, int32_t id, int32_t *count_out);
 
 /* Number of blocks whose reference count is 2 or more (retained for a second
- * table).  While it is 0 the decode kernels load every tile with a streaming
- * cache hint (see paged_attn_decode). */
+ * table).  While it is 0 (or a work list shows that few of a call's blocks can
+ * be such) the decode kernels load every tile with a streaming cache hint (see
+ * paged_attn_decode). */
 int kv_pool_num_shared(const pa_kv_pool *pool, int64_t *n_out);
 
 /* Geometry: element strides of the pool [block][kv_head][token][dim], and
@@ -171,8 +172,11 @@ int paged_attn_workspace_size(int32_t batch, int32_t num_q_heads, int32_t head_d
  * Both group sizes run on MFMA tiles.
  * Cache policy: when the pool holds no shared block (kv_pool_num_shared is 0),
  * no tile is read twice in a step and the kernels load the tiles with the
- * non-temporal hint; otherwise with the default policy, so that blocks shared
- * by several tables stay cached.  Tables that share blocks the allocator was
+ * non-temporal hint; so they do where a work list (paged_attn_decode_scheduled)
+ * shows that at most a tenth of a call's blocks can be shared ones, the pool's
+ * references to shared blocks against the call's full partitions, and the call
+ * reads more than 320 MB.  Otherwise they load with the default policy, so that
+ * blocks shared by several tables stay cached.  Tables that share blocks the allocator was
  * not told about give the same results, only possibly slower. */
 int paged_attn_decode(const pa_kv_pool *pool, const void *q, const int32_t *block_tables,
                       int32_t bt_stride, const int32_t *context_lens, int32_t batch,

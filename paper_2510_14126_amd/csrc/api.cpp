@@ -21,6 +21,7 @@ struct pa_kv_pool {
   std::vector<int32_t> refcount;  // 0 = free
   std::vector<int32_t> free_stack; // top = back(); ids pop in ascending order initially
   int64_t shared_blocks = 0;       // blocks whose reference count is 2 or more
+  int64_t shared_refs = 0;         // references of those blocks
 };
 
 namespace {
@@ -137,6 +138,29 @@ int validate_decode(const DecodeArgs& a, int32_t* group, const char* fn) {
 // partitions, while partition-major is faster for a few partitions).
 int32_t item_order_for(int32_t num_parts) { return num_parts >= 16 ? 1 : 0; }
 
+// Whether the plain decode loads its tiles with the streaming cache hint.
+// With no block shared by two tables every tile is read once per step.  With
+// shared blocks the hint costs their re-reads, and the host does not see a
+// call's tables; but a call holds at most the pool's references to shared
+// blocks, and a work list bounds its blocks from below (every partition of a
+// sequence but the last is full).  The hint is given where at most a tenth of
+// the call's references can be to shared blocks.  Whole step, default / streaming,
+// eight KV heads, 512-token partitions, share 5% / 10% / 20% / 33%: 192 sequences
+// of 64..8192 tokens, four heads per KV head 223 / 203 us, 224 / 204, 227 / 212, 233 /
+// 228; 48 of 8K-28K 663 / 603, 668 / 630, 684 / 698, 697 / 801, eight heads 696 / 620,
+// 709 / 651, 727 / 726, 791 / 811; 128 of 2K-4K in 256-token partitions 305 / 288, 307 /
+// 297, 310 / 321, 318 / 361.  Calls whose blocks may stay in the 256 MB Infinity Cache
+// from one to the next keep the default: one batch again and again, share 5%, 24
+// sequences of 2.7K-3.7K tokens (300 MB) 49.0 / 51.9 us, in 256-token partitions 49.0 /
+// 56.6; 32 of them (395 MB) 77.5 / 67.7 and 81.4 / 74.5.
+constexpr int64_t kStreamBytes = (int64_t)320 << 20;
+bool stream_tiles(const DecodeArgs& a, int32_t part_tokens, int32_t num_items) {
+  if (a.pool->shared_blocks == 0) return true;
+  const int64_t blocks = ((int64_t)num_items - a.batch) * (part_tokens / PA_BLOCK_SIZE);
+  const int64_t block_bytes = (int64_t)a.pool->num_kv_heads * PA_BLOCK_SIZE * a.pool->head_dim * 2 * 2;
+  return 10 * a.pool->shared_refs <= blocks && blocks * block_bytes >= kStreamBytes;
+}
+
 pa::DecodeParams decode_params(const DecodeArgs& a) {
   pa::DecodeParams p{};
   p.k_pool = a.pool->k;
@@ -151,9 +175,6 @@ pa::DecodeParams decode_params(const DecodeArgs& a) {
   p.batch = a.batch;
   p.bt_stride = a.bt_stride;
   p.max_ctx = a.max_context_len;
-  // With no block shared by two tables every tile is read once per step:
-  // stream it past the caches.
-  p.stream_tiles = a.pool->shared_blocks == 0 ? 1 : 0;
   p.scale_log2 = a.scale * 1.4426950408889634f;
   if (a.k_new) {
     p.k_new = static_cast<const uint16_t*>(a.k_new);
@@ -213,6 +234,7 @@ int decode_impl(const DecodeArgs& a, int32_t partition_size, void* out, float* p
   p.part_o = partial_out;
   p.part_lse = partial_lse;
   p.trace = trace;
+  p.stream_tiles = stream_tiles(a, pl.part_tokens, scheduled ? num_items : 0) ? 1 : 0;
   p.part_tokens = pl.part_tokens;
   p.num_parts = pl.num_parts;
   p.item_order = item_order_for(pl.num_parts);
@@ -374,8 +396,11 @@ int kv_pool_retain(pa_kv_pool* pool, int32_t n, const int32_t* ids) {
     if (pool->refcount[ids[i]] == 0x7fffffff)
       return fail(PA_ESTATE, "kv_pool_retain: reference count of block %d overflows", ids[i]);
   }
-  for (int32_t i = 0; i < n; ++i)
-    if (++pool->refcount[ids[i]] == 2) ++pool->shared_blocks;
+  for (int32_t i = 0; i < n; ++i) {
+    const bool second = ++pool->refcount[ids[i]] == 2;
+    if (second) ++pool->shared_blocks;
+    pool->shared_refs += second ? 2 : 1;
+  }
   return PA_OK;
 }
 
@@ -391,6 +416,7 @@ int kv_pool_release(pa_kv_pool* pool, int32_t n, const int32_t* ids) {
     const int32_t left = --pool->refcount[ids[i]];
     if (left == 0) freed = true;
     if (left == 1) --pool->shared_blocks;
+    if (left > 0) pool->shared_refs -= left == 1 ? 2 : 1;
   }
   if (freed) rebuild_free(pool);
   return PA_OK;
@@ -615,6 +641,7 @@ int cascade_impl(const pa_kv_pool* pool, const void* q, const int32_t* block_tab
   pa::DecodeParams p = decode_params(a);
   p.part_o = partial_out;
   p.part_lse = partial_lse;
+  p.stream_tiles = stream_tiles(a, cp.suf_tokens, scheduled ? num_items : 0) ? 1 : 0;
   p.part_tokens = cp.suf_tokens;
   p.num_parts = cp.suf_parts;
   p.item_order = item_order_for(cp.suf_parts);

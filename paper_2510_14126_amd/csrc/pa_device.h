@@ -58,14 +58,14 @@ __device__ __forceinline__ void store_partial4(float* dst, float a, float b, flo
 
 // Cache-policy operand of a buffer load: bit 1 is the non-temporal hint of
 // the gfx940 family.  Tiles that one step reads exactly once (a sequence's
-// tokens after what the batch shares, in the cascade; every tile when the
-// pool holds no shared block) are loaded with it, so they do not push lines
-// that are still in use out of L2 and the infinity cache: 8-11% of the
-// decode time on the long-context and shared-pool batches.  A line must be
-// read whole by one instruction: one read in parts by several instructions
-// can be evicted between them and fetched again.  Where blocks are shared
-// between sequences the plain decode keeps the default (the hint cost 5%
-// there on the long-context batch).
+// tokens after what the batch shares, in the cascade; every tile of a plain
+// decode where no or few blocks can be shared, stream_tiles in api.cpp) are
+// loaded with it, so they do not push lines that are still in use out of L2
+// and the infinity cache: 8-11% of the decode time on the long-context and
+// shared-pool batches.  A line must be read whole by one instruction: one read
+// in parts by several instructions can be evicted between them and fetched
+// again.  Where more blocks are shared the plain decode keeps the default (the
+// hint cost 5% there on the long-context batch).
 constexpr int kLoadDefault = 0;
 constexpr int kLoadStreaming = 2;
 
