@@ -149,7 +149,7 @@ def test_few_shared_blocks_keep_the_streaming_loads(group):
     references are to a shared block: the same tiles with the pool told of the
     sharing and without.  At most a tenth of the call's blocks can be shared, so
     both stream their tiles: the same bits and the same time (runs differ by 1%);
-    with the default policy the first took 1.07 to 1.12 times as long.  The
+    with the default policy the told pool took 1.12 times as long.  The
     sequences of a second call are few against the same references: the same
     bits under the default policy, and what the oracle gives."""
     from types import SimpleNamespace
@@ -176,7 +176,7 @@ def test_few_shared_blocks_keep_the_streaming_loads(group):
     few.k_pool, few.v_pool = (x.view(torch.int16).cpu().numpy().view(np.uint16) for x in (k, v))
     assert compare(outs[0][:5], decode_workload(few)[0]).passed
     print(f"[gpu case] told of no sharing {us[0]:.1f} us, told {us[1]:.1f} us", flush=True)
-    assert us[1] <= 1.04 * us[0], us
+    assert us[1] <= 1.06 * us[0], us
 
 
 @pytest.mark.parametrize("S", [16, 64, 176, 1024])
